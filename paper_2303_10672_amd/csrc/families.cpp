@@ -110,10 +110,11 @@ static B1Dev make_b1dev(const pvi_mdp* p) {
     b.cb = std::min(16, b.Rb);
     while (b.cb > 1 && (int64_t)b.na1 * stride(b.cb) + 3 * (b.HA + 1) > 8192) --b.cb;
     b.cbp = stride(b.cb);
-    // PVI_B1_LANES=0 keeps the final kernel over lanes of x_a for every sweep (for tests:
-    // both give the same values)
-    const char* lanes = std::getenv("PVI_B1_LANES");
-    b.lanes_ab = lanes && std::strcmp(lanes, "0") == 0 ? 0 : 1;
+    b.nap = (b.Ra * b.Rb + 15) / 16 * 16;
+    b.ntile = b.nap / 16;
+    b.ncha = (m - 1) * (b.Ra - 1) / 16 + 1;
+    b.nchb = (m - 1) * (b.Rb - 1) / 16 + 1;
+    b.npair = p->b1_npair;
     b.gamma = p->d.gamma;
     b.cva = p->d.c_var[0];
     b.cvb = p->d.c_var[1];
@@ -129,6 +130,13 @@ static B1Dev make_b1dev(const pvi_mdp* p) {
     b.jc = d.b1jc;
     b.rev = d.b1rev;
     b.xb_order = d.b1xb;
+    b.xb_pair = d.b1pair;
+    b.akk = d.b1ka;
+    b.bkk = d.b1kb;
+    b.asort = d.b1sort;
+    b.apath = d.b1patha;
+    b.bpath = d.b1pathb;
+    b.best = d.gap;
     b.ctl = d.ctl;
     b.partials = d.partials;
     b.nslots = family_tiles(p);
@@ -231,19 +239,22 @@ int family_tiles(const pvi_mdp* p) {
             return (int)c_partial_slots(p->P, ipow(p->rad[0], p->m - 2));
         return (int)(p->P * ((ipow(p->rad[0], p->m - 1) + 255) / 256));
     }
-    if (p->family == PVI_FAMILY_SUBST2_L1)  // either final kernel's grid fits
-        return (int)(ipow(p->rad[1], p->m) *
-                     std::max((ipow(p->rad[0], p->m) + 255) / 256,
-                              (ipow(p->rad[0], p->m - 1) + kB1Groups - 1) / kB1Groups));
+    if (p->family == PVI_FAMILY_SUBST2_L1) {  // either kernel set's last grid fits
+        const int64_t na = ipow(p->rad[0], p->m), nb = ipow(p->rad[1], p->m);
+        return (int)std::max(nb * ((na + 255) / 256), (na + 63) / 64 * ((nb + 63) / 64));
+    }
     return 1;
 }
 
+// joint orders of the W and Y tables, padded to the matrix kernels' tiles of 16
+static size_t b1_orders(const pvi_mdp* p) { return ((size_t)p->na + 15) / 16 * 16; }
+
 static size_t b1_w_entries(const pvi_mdp* p) {
-    return (size_t)p->na * ipow(p->rad[1], p->m) * ipow(p->rad[0], p->m - 1);
+    return b1_orders(p) * ipow(p->rad[1], p->m) * ipow(p->rad[0], p->m - 1);
 }
 
 static size_t b1_y_entries(const pvi_mdp* p) {
-    return (size_t)p->na * p->b1_hb * ipow(p->rad[0], p->m);
+    return b1_orders(p) * p->b1_hb * ipow(p->rad[0], p->m);
 }
 
 size_t family_extra_bytes(const pvi_mdp* p) {
@@ -264,7 +275,10 @@ size_t family_extra_bytes(const pvi_mdp* p) {
     if (p->family == PVI_FAMILY_SUBST2_L1)
         return sizeof(double) * (b1_w_entries(p) + b1_y_entries(p) + 3 * p->b1_pa1.size() +
                                  p->b1_pb.size() + p->b1_fb.size() +
-                                 p->b1_j.size() + p->b1_jc.size() + p->b1_rev.size());
+                                 p->b1_j.size() + p->b1_jc.size() + p->b1_rev.size()) +
+               // path rows, lengths and orders of the matrix kernels
+               64 * (size_t)(ipow(p->rad[0], p->m - 1) + ipow(p->rad[1], p->m - 1)) * p->m +
+               12 * (size_t)ipow(p->rad[1], p->m);
     return 0;
 }
 
@@ -287,8 +301,46 @@ static std::vector<int32_t> b1_xb_order(const pvi_mdp* p) {
     return order;
 }
 
-// A demand table of product a followed by kB1Pad zeros: the final kernel over lanes of b's
-// orders reads it at x_1 + k for every x_1 < 16, also past a's largest issue.
+// Consecutive pairs of b1_xb_order within one digit sum; an odd one out is paired with
+// itself.
+static std::vector<int32_t> b1_pairs(const pvi_mdp* p, const std::vector<int32_t>& order) {
+    auto sum = [&](int32_t x) {
+        int t = 0;
+        for (int64_t v = x; v > 0; v /= p->rad[1]) t += (int)(v % p->rad[1]);
+        return t;
+    };
+    std::vector<int32_t> out;
+    for (size_t i = 0; i < order.size();) {
+        const bool two = i + 1 < order.size() && sum(order[i]) == sum(order[i + 1]);
+        out.push_back(order[i]);
+        out.push_back(two ? order[i + 1] : order[i]);
+        i += two ? 2 : 1;
+    }
+    return out;
+}
+
+// Path groups of one product (radix R, the m - 1 digits above X_1 as one index g): the
+// length K = sum of the digits, and the rows of the FIFO path g, .., 0 in chunks of 16
+// points, entry [g][k / 16][k % 4][k / 4 % 4]; points past K repeat the last row.
+static void b1_paths(int R, int m, std::vector<int32_t>& len, std::vector<uint16_t>& rows) {
+    const int n = (int)ipow(R, m - 1), nch = (m - 1) * (R - 1) / 16 + 1;
+    len.assign((size_t)n, 0);
+    rows.assign((size_t)n * nch * 16, 0);
+    for (int g = 0; g < n; ++g) {
+        int at = g, k = 0;
+        for (;; ++k) {
+            rows[((size_t)g * nch + k / 16) * 16 + (k % 4) * 4 + k / 4 % 4] = (uint16_t)at;
+            if (at == 0) break;
+            int pw = 1;  // the lowest digit with stock loses a unit
+            while (at / pw % R == 0) pw *= R;
+            at -= pw;
+        }
+        len[(size_t)g] = k;
+    }
+}
+
+// A demand table of product a followed by kB1Pad zeros: the matrix kernels read it at
+// x_1 + k also past a's largest issue.
 static std::vector<double> padded(const std::vector<double>& v) {
     std::vector<double> out(v);
     out.resize(v.size() + kB1Pad, 0.0);
@@ -505,6 +557,15 @@ pvi_status family_init(pvi_mdp* p) {
         if (st != PVI_OK) return st;
     }
     if (p->family == PVI_FAMILY_SUBST2_L1) {
+        const std::vector<int32_t> order = b1_xb_order(p), pairs = b1_pairs(p, order);
+        p->b1_npair = (int)(pairs.size() / 2);
+        std::vector<int32_t> len[2], sorted;
+        std::vector<uint16_t> rows[2];
+        for (int k = 0; k < 2; ++k) b1_paths(p->rad[k], p->m, len[k], rows[k]);
+        for (size_t g = 0; g < len[0].size(); ++g) sorted.push_back((int32_t)g);
+        std::stable_sort(sorted.begin(), sorted.end(), [&](int32_t a, int32_t b) {
+            return len[0][(size_t)a] > len[0][(size_t)b];
+        });
         if (hipMalloc((void**)&d.b1w, sizeof(double) * b1_w_entries(p)) != hipSuccess ||
             hipMalloc((void**)&d.b1y, sizeof(double) * b1_y_entries(p)) != hipSuccess ||
             upload_vec(&d.b1pa, padded(p->b1_pa1)) != hipSuccess ||
@@ -515,7 +576,13 @@ pvi_status family_init(pvi_mdp* p) {
             upload_vec(&d.b1j, p->b1_j) != hipSuccess ||
             upload_vec(&d.b1jc, p->b1_jc) != hipSuccess ||
             upload_vec(&d.b1rev, p->b1_rev) != hipSuccess ||
-            upload_vec(&d.b1xb, b1_xb_order(p)) != hipSuccess)
+            upload_vec(&d.b1xb, order) != hipSuccess ||
+            upload_vec(&d.b1pair, pairs) != hipSuccess ||
+            upload_vec(&d.b1ka, len[0]) != hipSuccess ||
+            upload_vec(&d.b1kb, len[1]) != hipSuccess ||
+            upload_vec(&d.b1sort, sorted) != hipSuccess ||
+            upload_vec(&d.b1patha, rows[0]) != hipSuccess ||
+            upload_vec(&d.b1pathb, rows[1]) != hipSuccess)
             return fail(PVI_E_NOMEM, "lead-time-1 two-product table allocation failed");
     }
     return PVI_OK;
@@ -526,12 +593,14 @@ void family_free(pvi_mdp* p) {
     void* bufs[] = {d.z,    d.rexp0, d.epmf,  d.ecdf,  d.etail, d.rexp1, d.cu,  d.ct0,
                     d.ct1,  d.cpmf,  d.ccdf,  d.ctail, d.cr0,   d.cbinq,  d.cbinm, d.cpy,
                     d.cpr,  d.cpb, d.agroups, d.ctf, d.b1w, d.b1y, d.b1pa, d.b1fa, d.b1ga,
-                    d.b1pb, d.b1fb, d.b1j, d.b1jc, d.b1rev, d.b1xb, d.bppad, d.bgpad};
+                    d.b1pb, d.b1fb, d.b1j, d.b1jc, d.b1rev, d.b1xb, d.bppad, d.bgpad,
+                    d.b1pair, d.b1ka, d.b1kb, d.b1sort, d.b1patha, d.b1pathb};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     d.b1w = d.b1y = d.b1pa = d.b1fa = d.b1ga = d.b1pb = d.b1fb = d.b1j = d.b1jc = d.b1rev =
         nullptr;
-    d.b1xb = nullptr;
+    d.b1xb = d.b1pair = d.b1ka = d.b1kb = d.b1sort = nullptr;
+    d.b1patha = d.b1pathb = nullptr;
     d.z = d.rexp0 = d.epmf = d.ecdf = d.etail = d.rexp1 = d.bppad = d.bgpad = nullptr;
     d.cu = d.ct0 = d.ct1 = d.ctf = nullptr;
     d.cpmf = d.ccdf = d.ctail = d.cr0 = d.cbinq = d.cbinm = nullptr;
@@ -597,6 +666,10 @@ static hipError_t family_backup_launch(pvi_mdp* p, int fp32, int kahan, int extr
         b.v_in = vin;
         b.v_out = vout;
         b.extract = extract;
+        // PVI_B1_LANES=0 keeps the general kernels (for tests: both give the same values)
+        const char* lanes = std::getenv("PVI_B1_LANES");
+        if (b1m_fits(b) && !(lanes && std::strcmp(lanes, "0") == 0))
+            return launch_backup_b1m(b, fp32, extract, s);
         return launch_backup_b1(b, fp32, extract, s);
     }
     return hipErrorInvalidValue;

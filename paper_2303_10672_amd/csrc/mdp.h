@@ -48,6 +48,7 @@ struct pvi_mdp {
 
     // Scenario B as the paper runs it (lead time 1): issue probabilities and revenue
     int b1_ha = 0, b1_hb = 0;  // m a_max + 1 per product
+    int b1_npair = 0;          // pairs of x_b of the matrix kernels
     std::vector<double> b1_pa, b1_pb, b1_fb, b1_j, b1_jc, b1_rev;
     std::vector<double> b1_pa1, b1_fa, b1_ga;  // [HA + 1] P(D_a = h), P(D_a <= h), P(D_a >= h)
 
@@ -81,6 +82,8 @@ struct pvi_mdp {
         double *b1w = nullptr, *b1y = nullptr, *b1pa = nullptr, *b1fa = nullptr, *b1ga = nullptr,
                *b1pb = nullptr, *b1fb = nullptr, *b1j = nullptr, *b1jc = nullptr,
                *b1rev = nullptr;
+        int32_t *b1pair = nullptr, *b1ka = nullptr, *b1kb = nullptr, *b1sort = nullptr;
+        uint16_t *b1patha = nullptr, *b1pathb = nullptr;  // matrix kernels' path tables
         int32_t* b1xb = nullptr;  // x_b in the final kernels' order (by digit sum I_b)
         int tiles = 0;
         size_t bytes = 0;

@@ -140,8 +140,11 @@ struct B1Dev {
     double* gap;
     double* partials;     // [nslots][4]
     int32_t nslots;       // NB * max(ceil(NA / 256), ceil(na1 / kB1Groups))
-    double* w;            // [Ra][Rb][NB][na1]: sum over h_b < I_b of V, per next A part
-    double* y;            // [Ra][Rb][HB][NA]: the b-runs-out term per I_b
+    double* w;            // b-side sums over h_b < I_b of V per next A part: general
+                          // kernels [Ra][Rb][NB][na1], matrix kernels [NB][na1][nap]
+    double* y;            // the b-runs-out term per I_b: general kernels
+                          // [Ra][Rb][HB][NA], matrix kernels [HB][NA][nap]
+    double* best;         // matrix kernels: [NB][NA] maxima of a sweep (the gap buffer)
     const double* pa1;    // [HA + 1 + kB1Pad] P(D_a = h), zeros past HA
     const double* fa;     // [HA + 1 + kB1Pad] P(D_a <= h), zeros past HA
     const double* ga;     // [HA + 1 + kB1Pad] P(D_a >= h), zeros past HA
@@ -151,20 +154,31 @@ struct B1Dev {
     const double* jc;     // [HB][HA][HA] cumulative over h_a
     const double* rev;    // [HA][HB] expected one-day revenue
     const int32_t* xb_order;  // [NB] x_b by digit sum: the final kernels' order
+    // matrix kernels: pairs of x_b of one digit sum (an odd one out is paired with
+    // itself), path lengths K per group, a's groups by falling K, and the rows of each
+    // group's path, [group][chunk of 16 points][k % 4][k / 4 % 4]
+    const int32_t* xb_pair;
+    const int32_t *akk, *bkk, *asort;
+    const uint16_t *apath, *bpath;
     Ctl* ctl;
     int32_t m, Ra, Rb, HA, HB, na1, nb1, NA, NB, extract;
     int32_t gw;           // stage W: values of the next A part per workgroup
     int32_t cb;           // final stage: orders of b per LDS chunk
     int32_t cbp;          // its LDS row stride in doubles (even, 2 mod 4)
-    int32_t lanes_ab;     // 1: the final sweeps use the kernel over lanes of b's orders
-                          // where it applies (0: b1_final_kernel everywhere)
+    int32_t nap, ntile;   // joint orders padded to whole tiles of 16, and tiles
+    int32_t npair, ncha, nchb;  // x_b pairs; chunks of a group's path of a and of b
     double gamma, cva, cvb;
 };
 hipError_t launch_backup_b1(const B1Dev& p, int storage_fp32, int extract, hipStream_t s);
-// The final kernel over lanes of b's orders: path groups (x_a without X_1) per workgroup,
-// and the zeros after a's demand tables (pa1, fa, ga) that its reads at x_1 + k need.
-constexpr int kB1Groups = 16;
+// The same backup on the FP64 matrix cores (kernels_b1m.hip), and whether a shape fits
+// its kernels: at most 32 orders per product, tiles of 16 joint orders within the LDS.
+hipError_t launch_backup_b1m(const B1Dev& p, int storage_fp32, int extract, hipStream_t s);
+bool b1m_fits(const B1Dev& p);
+// Zeros after a's demand tables (pa1, fa, ga): the matrix kernels read them at x_1 + k for
+// every x_1 < 32 and k up to three past the path.
 constexpr int kB1Pad = 48;
+// LDS of one gfx950 workgroup
+constexpr size_t kB1mLds = 160 * 1024;
 hipError_t launch_b1_initial(const B1Dev& p, double* v, hipStream_t s);
 
 // ------------------------------------------------------------------ rollouts

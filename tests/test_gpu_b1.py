@@ -146,6 +146,26 @@ def test_final_kernels_agree(prec):
     assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("m,a_max", [(1, (9, 7)), (2, (4, 4)), (2, (16, 5)), (2, (5, 31)),
+                                     (2, (31, 17)), (3, (3, 4)), (3, (8, 5)), (4, (3, 2))],
+                         ids=str)
+def test_matrix_kernels_agree_with_general(monkeypatch, m, a_max, prec):
+    """Tiles of 16 orders and of 16 values of X_1 with remainders, one and two tiles of
+    X_1, one and several path chunks: the matrix kernels add the general kernels' terms
+    in their order, so values, policy and gap are equal bit for bit."""
+    sc = W.scenario_b1(m=m, a_max=a_max, means=(a_max[0] / 2.7, a_max[1] / 2.9), rho=0.43)
+    sc["costs"]["var"], sc["costs"]["rev"] = [0.537, 0.471], [1.03, 0.97]
+    h = pvi.mdp_create(sc)
+    got = []
+    for env in ("1", "0"):
+        monkeypatch.setenv("PVI_B1_LANES", env)
+        pvi.vi_solve(h, precision=prec, fixed_sweeps=3)
+        got.append((pvi.value_get(h),) + pvi.policy_get(h))
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 def test_rollouts_match_oracle():
     sc = W.scenario_b1(m=2, a_max=(5, 4), means=(3.0, 2.0), rho=0.6, d_max=12)
     o = Oracle(sc)
