@@ -150,6 +150,11 @@ hipError_t family_initial_values(pvi_mdp* p, double* v, hipStream_t s) {
     return launch_b1_initial(make_b1dev(p), v, s);
 }
 
+// Low-digit values R^(m-2) of the level the top merge reads, padded to lines of 16.
+static int64_t c_top_lo(const pvi_mdp* p) {
+    return p->m >= 4 ? (ipow(p->rad[0], p->m - 2) + 15) / 16 * 16 : 0;
+}
+
 static CDev make_cdev(const pvi_mdp* p) {
     CDev c{};
     const int R = p->rad[0];
@@ -170,7 +175,12 @@ static CDev make_cdev(const pvi_mdp* p) {
     c.u = d.cu;
     c.t0 = d.ct0;
     c.t1 = d.ct1;
-    c.tf = d.ctf;
+    c.tf = p->c_tri ? nullptr : d.ctf;
+    c.sec = p->c_tri ? static_cast<double*>(d.ctf) : nullptr;
+    c.tri = p->c_tri ? 1 : 0;
+    c.tlo = (int32_t)c_top_lo(p);
+    c.trow = (int64_t)R * c.tlo;
+    c.orow = c.nblk;
     std::memcpy(c.lb, p->c_lb, sizeof(c.lb));
     c.exogenous = p->c_exogenous ? 1 : 0;
     c.alim = R - 1;
@@ -181,6 +191,9 @@ static CDev make_cdev(const pvi_mdp* p) {
     c.r0 = d.cr0;
     c.binq = d.cbinq;
     c.binm = d.cbinm;
+    c.binp = d.cbinp;
+    c.binmp = d.cbinmp;
+    c.swap23 = p->c_tri && p->m == 5 && c_merge23_tri_fits<double>(c) ? 1 : 0;
     c.pair_y = d.cpy;
     c.pair_r = d.cpr;
     c.pair_base = d.cpb;
@@ -192,7 +205,8 @@ static CDev make_cdev(const pvi_mdp* p) {
 }
 
 static size_t c_table_entries(const pvi_mdp* p) {  // entries of one merge table
-    return (size_t)p->P * p->c_npair * ipow(p->rad[0], p->m - 1);
+    const int64_t row = std::max(ipow(p->rad[0], p->m - 1), p->rad[0] * c_top_lo(p));
+    return (size_t)p->P * p->c_npair * row;
 }
 
 std::string family_support_msg(const pvi_mdp* p) {
@@ -237,7 +251,9 @@ int family_tiles(const pvi_mdp* p) {
     if (p->family == PVI_FAMILY_RUL_WEEKDAY) {
         if (p->m >= 4 && p->c_exogenous)  // top merge fused with the final sum
             return (int)c_partial_slots(p->P, ipow(p->rad[0], p->m - 2));
-        return (int)(p->P * ((ipow(p->rad[0], p->m - 1) + 255) / 256));
+        // one per 64 states of the order-dependent kernels, per 256 of the others
+        const int per = p->c_tri && !p->c_exogenous ? 64 : 256;
+        return (int)(p->P * ((ipow(p->rad[0], p->m - 1) + per - 1) / per));
     }
     if (p->family == PVI_FAMILY_SUBST2_L1) {  // either kernel set's last grid fits
         const int64_t na = ipow(p->rad[0], p->m), nb = ipow(p->rad[1], p->m);
@@ -270,7 +286,7 @@ size_t family_extra_bytes(const pvi_mdp* p) {
         const size_t tt = p->m >= 3 ? c_table_entries(p) : 0;
         const size_t ntab = p->c_exogenous ? 2 : 3;
         return sizeof(double) * (ut + ntab * tt + 3 * p->c_pmf.size() + p->c_r0.size() +
-                                 p->c_binq.size() + p->c_binm.size());
+                                 5 * p->c_binq.size() + p->c_binm.size() + 2080);
     }
     if (p->family == PVI_FAMILY_SUBST2_L1)
         return sizeof(double) * (b1_w_entries(p) + b1_y_entries(p) + 3 * p->b1_pa1.size() +
@@ -383,6 +399,9 @@ pvi_status tune_c(pvi_mdp* p) {
     }
     const char* env = std::getenv("PVI_TUNE");
     if ((env && std::strcmp(env, "0") == 0) || p->m < 4) return PVI_OK;
+    // no width to choose where every merge from level 3 on is an antidiagonal kernel
+    if (p->c_tri && (p->m == 4 || (p->m == 5 && c_merge23_tri_fits<double>(make_cdev(p)))))
+        return PVI_OK;
     const TuneKey key{p->rad[0], p->m, p->P};
     std::lock_guard<std::mutex> lock(g_tune_mu);
     auto it = g_tune.find(key);
@@ -539,15 +558,29 @@ pvi_status family_init(pvi_mdp* p) {
     if (p->family == PVI_FAMILY_RUL_WEEKDAY) {
         const size_t ut = (size_t)p->ns * p->rad[0];
         const size_t tt = p->m >= 3 ? c_table_entries(p) : 1;
+        const size_t tft = p->c_tri ? (size_t)p->ns : tt;
+        // their weights: each level's triangle packed, and Bin(y; a, p_m) in padded rows
+        const int R = p->rad[0], rc = c_tri_bound(R);
+        const size_t nlev = p->c_binq.size() / ((size_t)R * R), nw = c_tri_weights(R);
+        std::vector<double> binp(p->c_tri ? nlev * nw : 1, 0.0),
+            binmp((size_t)(2 * rc + 1) * rc, 0.0);
+        for (int r = 0; r < R && p->c_tri; ++r)
+            for (int y = 0; y <= r; ++y) {
+                for (size_t b = 0; b < nlev; ++b)
+                    binp[b * nw + r * (r + 1) / 2 + y] = p->c_binq[b * R * R + r * R + y];
+                binmp[(size_t)r * rc + y] = p->c_binm[(size_t)r * R + y];
+            }
         if (hipMalloc(&d.cu, sizeof(double) * ut) != hipSuccess ||
             hipMalloc(&d.ct0, sizeof(double) * tt) != hipSuccess ||
             hipMalloc(&d.ct1, sizeof(double) * tt) != hipSuccess ||
-            (!p->c_exogenous && hipMalloc(&d.ctf, sizeof(double) * tt) != hipSuccess) ||
+            (!p->c_exogenous && hipMalloc(&d.ctf, sizeof(double) * tft) != hipSuccess) ||
             upload_vec(&d.cpmf, p->c_pmf) != hipSuccess ||
             upload_vec(&d.ccdf, p->c_cdf) != hipSuccess ||
             upload_vec(&d.ctail, p->c_tail) != hipSuccess ||
             upload_vec(&d.cr0, p->c_r0) != hipSuccess ||
             upload_vec(&d.cbinq, p->c_binq) != hipSuccess ||
+            upload_vec(&d.cbinp, binp) != hipSuccess ||
+            upload_vec(&d.cbinmp, binmp) != hipSuccess ||
             upload_vec(&d.cbinm, p->c_binm) != hipSuccess ||
             upload_vec(&d.cpy, p->c_pair_y) != hipSuccess ||
             upload_vec(&d.cpr, p->c_pair_r) != hipSuccess ||
@@ -594,7 +627,7 @@ void family_free(pvi_mdp* p) {
                     d.ct1,  d.cpmf,  d.ccdf,  d.ctail, d.cr0,   d.cbinq,  d.cbinm, d.cpy,
                     d.cpr,  d.cpb, d.agroups, d.ctf, d.b1w, d.b1y, d.b1pa, d.b1fa, d.b1ga,
                     d.b1pb, d.b1fb, d.b1j, d.b1jc, d.b1rev, d.b1xb, d.bppad, d.bgpad,
-                    d.b1pair, d.b1ka, d.b1kb, d.b1sort, d.b1patha, d.b1pathb};
+                    d.cbinp, d.cbinmp, d.b1pair, d.b1ka, d.b1kb, d.b1sort, d.b1patha, d.b1pathb};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     d.b1w = d.b1y = d.b1pa = d.b1fa = d.b1ga = d.b1pb = d.b1fb = d.b1j = d.b1jc = d.b1rev =
@@ -603,6 +636,7 @@ void family_free(pvi_mdp* p) {
     d.b1patha = d.b1pathb = nullptr;
     d.z = d.rexp0 = d.epmf = d.ecdf = d.etail = d.rexp1 = d.bppad = d.bgpad = nullptr;
     d.cu = d.ct0 = d.ct1 = d.ctf = nullptr;
+    d.cbinp = d.cbinmp = nullptr;
     d.cpmf = d.ccdf = d.ctail = d.cr0 = d.cbinq = d.cbinm = nullptr;
     d.cpy = d.cpr = d.cpb = nullptr;
     d.agroups = nullptr;

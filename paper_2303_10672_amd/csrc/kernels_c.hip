@@ -163,9 +163,9 @@ __global__ __launch_bounds__(1024) void c_merge2_kernel(CDev p, const void* in_,
         o1[y] = min(x1 + y, R - 1);
     }
     const ConstF64 w = (ConstF64)(p.binq + (size_t)2 * R * R);
-    VT* T = reinterpret_cast<VT*>(out_) + ((int64_t)tau * p.npair + p.pair_base[ym]) * p.nblk +
-            hi * R * R + tid;
-    c_merge2_rows<VT, RC, 0>(slab, o2, o1, w, R, nr, p.top_only ? nr - 1 : 0, T, p.nblk);
+    VT* T = reinterpret_cast<VT*>(out_) + ((int64_t)tau * p.npair + p.pair_base[ym]) * p.orow +
+            hi * p.ohi + tid;
+    c_merge2_rows<VT, RC, 0>(slab, o2, o1, w, R, nr, p.top_only ? nr - 1 : 0, T, p.orow);
 }
 
 // Rows r .. nr-1 of one lane's merge output (rows below rfirst skipped), one row per
@@ -288,11 +288,12 @@ __global__ __launch_bounds__(1024) void c_merge_kernel(CDev p, int j, const void
     for (int y = 0; y < RC; ++y) zoff[y] = min(xz + y, R - 1) * LB + l;
     // weights Bin(y; r, q_j) at r R + y
     const ConstF64 w = (ConstF64)(p.binq + (size_t)j * R * R);
-    VT* out = reinterpret_cast<VT*>(out_) + row0 * p.nblk + base + (int64_t)xz * nlo + l;
+    VT* out = reinterpret_cast<VT*>(out_) + row0 * p.orow + hi * p.ohi + lo0 +
+              (int64_t)xz * nlo + l;
     if (p.top_only)
-        c_merge_rows<VT, LB, RC, 0>(slab, zoff, w, R, nr, nr - 1, out, p.nblk);
+        c_merge_rows<VT, LB, RC, 0>(slab, zoff, w, R, nr, nr - 1, out, p.orow);
     else
-        c_merge_rows4<VT, LB, RC, 0>(slab, zoff, w, R, nr, out, p.nblk);
+        c_merge_rows4<VT, LB, RC, 0>(slab, zoff, w, R, nr, out, p.orow);
 }
 
 // Orders a .. R-1 of one state's final sum (m >= 3), one order per template instance so
@@ -466,7 +467,7 @@ __global__ __launch_bounds__(kCFusedThreads) void c_merge23_kernel(CDev p, const
     const ConstF64 w2 = (ConstF64)(p.binq + (size_t)2 * R * R);
     const ConstF64 w3 = (ConstF64)(p.binq + (size_t)3 * R * R);
     VT* T = reinterpret_cast<VT*>(out_) +
-            ((int64_t)tau * p.npair + p.pair_base[ym]) * p.nblk + (int64_t)hi * R3 +
+            ((int64_t)tau * p.npair + p.pair_base[ym]) * p.orow + (int64_t)hi * p.ohi +
             (int64_t)xz * RR + l;
     const int nlob = (RR + LB - 1) / LB;
     __syncthreads();
@@ -485,7 +486,7 @@ __global__ __launch_bounds__(kCFusedThreads) void c_merge23_kernel(CDev p, const
                                       RS);
         }
         __syncthreads();
-        if (ok) c_merge_rows4<VT, LB, RC, 0>(slab, zoff, w3, R, nr, T + blk * LB, p.nblk);
+        if (ok) c_merge_rows4<VT, LB, RC, 0>(slab, zoff, w3, R, nr, T + blk * LB, p.orow);
         __syncthreads();
     }
 }
@@ -735,6 +736,14 @@ static hipError_t launch_top_final(const CDev& p, const void* in, int lb, hipStr
     return hipErrorInvalidValue;
 }
 
+// Output strides of merge level j: the layout the antidiagonal kernels read at level
+// m-2, else rows of nblk values and R^j values per step of the digits above.
+static void c_out_strides(CDev& p, int j) {
+    const bool top_in = p.tri && j == p.m - 2;
+    p.orow = top_in ? p.trow : p.nblk;
+    p.ohi = top_in ? p.tlo : (int64_t)p.pow_r[j];
+}
+
 template <typename VT, bool EXTRACT>
 static hipError_t launch_c_t(const CDev& p, hipStream_t s) {
     const size_t ubytes = sizeof(double) * ((size_t)p.lpmax + 3 * (size_t)p.tab);
@@ -748,6 +757,24 @@ static hipError_t launch_c_t(const CDev& p, hipStream_t s) {
     if (e != hipSuccess) return e;
     const unsigned gx = (unsigned)((p.nblk + 255) / 256);
     const void* tin = p.u;
+    if (p.tri) {
+        // the table of level m-2, then the top level and the final sum from it
+        tin = ((p.m - 2) & 1) ? p.t1 : p.t0;
+        if (p.exogenous) {
+            if ((e = launch_c_chain<VT>(p, nullptr, p.m - 2, s)) != hipSuccess) return e;
+            return launch_c_top<VT, EXTRACT>(p, tin, s);
+        }
+        for (int a = 0; a < p.R; ++a) {
+            CDev q = p;
+            q.binq = p.binq + (size_t)a * p.m * p.R * p.R;
+            q.binp = p.binp + (size_t)a * p.m * c_tri_weights(p.R);
+            q.alim = a;
+            if ((e = launch_c_chain<VT>(q, nullptr, p.m - 2, s)) != hipSuccess ||
+                (e = launch_c_order<VT, EXTRACT>(q, tin, a, s)) != hipSuccess)
+                return e;
+        }
+        return hipSuccess;
+    }
     if (!EXTRACT && p.m >= 4 && p.exogenous) {
         // levels 2 .. m-2, then the top level fused with the final sum
         if ((e = launch_c_chain<VT>(p, nullptr, p.m - 2, s)) != hipSuccess) return e;
@@ -794,11 +821,16 @@ static hipError_t launch_c_chain(const CDev& p, void* top, int jlast, hipStream_
             q.top_only = 1;
             out = top;
         }
-        if (j == 2 && jlast >= 3 && c_use23<VT>(p, c_level_lb<VT>(p, 3))) {
+        const bool tri23 = p.tri && j == 2 && jlast >= 3 && c_merge23_tri_fits<double>(p);
+        const bool plain23 = !tri23 && j == 2 && jlast >= 3 && c_use23<VT>(p, c_level_lb<VT>(p, 3));
+        // the last level written (levels 2 and 3 come together where fused)
+        c_out_strides(q, tri23 || plain23 ? 3 : j);
+        if (tri23 || plain23) {
             // levels 2 and 3 in one kernel, T_3 into level 3's table
             out = bufs[1];
-            if ((e = launch_merge23<VT>(p, in, out, c_level_lb<VT>(p, 3), s)) != hipSuccess)
-                return e;
+            e = tri23 ? launch_merge23_tri<VT>(q, in, out, s)
+                      : launch_merge23<VT>(q, in, out, c_level_lb<VT>(p, 3), s);
+            if (e != hipSuccess) return e;
             in = out;
             ++j;
             continue;
@@ -877,7 +909,9 @@ static hipError_t launch_merge_once(const CDev& p, int j, int lb, hipStream_t s)
     if (nwg > 0x7fffffff || nlo * p.R > 0x7fffffff || p.R > 32 ||
         c_lds_for<VT>(p, lb) > 65536 || p.R * lb > 1024)
         return hipErrorInvalidConfiguration;
-    return launch_merge_lb<VT>(p, j, p.t0, p.t1, lb, dim3((unsigned)nwg), threads,
+    CDev q = p;
+    c_out_strides(q, j);
+    return launch_merge_lb<VT>(q, j, p.t0, p.t1, lb, dim3((unsigned)nwg), threads,
                                c_lds_for<VT>(p, lb), s);
 }
 
@@ -895,7 +929,9 @@ static hipError_t launch_level_once(const CDev& p, int j, int lb, hipStream_t s)
     if (j == 3 && p.m >= 5) {
         // level 3 runs fused with level 2 where it fits; otherwise the first merge is
         // timed with it, so that every width is timed on the same work
-        if (c_use23<VT>(p, lb)) return launch_merge23<VT>(p, p.u, p.t1, lb, s);
+        CDev q = p;
+        c_out_strides(q, 3);
+        if (c_use23<VT>(p, lb)) return launch_merge23<VT>(q, p.u, p.t1, lb, s);
         hipError_t e = launch_c_chain<VT>(p, nullptr, 2, s);  // U into t0
         if (e != hipSuccess) return e;
     }
@@ -942,6 +978,7 @@ hipError_t tune_c_merge(const CDev& pin, hipStream_t s, int32_t lb[2][10]) {
     p.extract = 1;  // the merge kernels then ignore the stop flag
     p.alim = p.R - 1;
     p.top_only = 0;
+    p.tri = 0;  // the plain kernels' layouts (no larger than the padded ones)
     for (int v = 0; v < 2; ++v)
         for (int j = 0; j < 10; ++j) lb[v][j] = 0;
     if (p.m < 4) return hipSuccess;  // no level j >= 3

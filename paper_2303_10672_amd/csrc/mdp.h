@@ -41,6 +41,7 @@ struct pvi_mdp {
 
     // Scenario C kernel tables
     bool c_exogenous = true;
+    bool c_tri = false;  // merges by antidiagonals (kernels_ct.hip)
     int32_t c_lb[2][10] = {};  // merge block width per [FP32 storage][level] (0: LDS rule)
     int c_tab = 0, c_xt = 0, c_lpmax = 0, c_npair = 0;
     std::vector<double> c_pmf, c_cdf, c_tail, c_r0, c_binq, c_binm;
@@ -77,7 +78,7 @@ struct pvi_mdp {
                *etail = nullptr, *rexp1 = nullptr, *bppad = nullptr, *bgpad = nullptr;
         void *cu = nullptr, *ct0 = nullptr, *ct1 = nullptr, *ctf = nullptr;
         double *cpmf = nullptr, *ccdf = nullptr, *ctail = nullptr, *cr0 = nullptr,
-               *cbinq = nullptr, *cbinm = nullptr;
+               *cbinq = nullptr, *cbinm = nullptr, *cbinp = nullptr, *cbinmp = nullptr;
         int32_t *cpy = nullptr, *cpr = nullptr, *cpb = nullptr;
         double *b1w = nullptr, *b1y = nullptr, *b1pa = nullptr, *b1fa = nullptr, *b1ga = nullptr,
                *b1pb = nullptr, *b1fb = nullptr, *b1j = nullptr, *b1jc = nullptr,

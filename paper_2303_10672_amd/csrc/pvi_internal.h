@@ -110,7 +110,9 @@ struct CDev {
     void* u;              // U[tau][z_m][z_{m-1}..z_1]
     void* t0;             // merge ping-pong tables [tau][(y_m, r)][digits]
     void* t1;
-    void* tf;             // order-dependent life: top-level rows r = a - y_m of every a
+    void* tf;             // order-dependent life, plain kernels: top-level rows r = a - y_m
+                          // of every a
+    double* sec;          // order-dependent life, extraction: [ns] second best so far
     const double* pmf;    // [P][tab] per-weekday demand, zero past d_max
     const double* cdf;    // [P][tab], one past d_max
     const double* tail;   // [P][tab], zero past d_max
@@ -118,11 +120,21 @@ struct CDev {
     const double* binq;   // [m][R][R] Bin(y; r, q_j) (for one order size a when the
                           // life distribution depends on it)
     const double* binm;   // [R][R] Bin(y; a, p_m(a))
+    const double* binp;   // antidiagonal kernels: the triangles of binq packed row by row,
+                          // [m][c_tri_weights(R)]
+    const double* binmp;  // and binm with rows of c_tri_bound(R), zeros past its entries
     const int32_t* pair_y;
     const int32_t* pair_r;
     const int32_t* pair_base;
     Ctl* ctl;
     int64_t nblk;         // R^(m-1) states per weekday
+    // antidiagonal kernels (tri = 1): layout of the table of level m-2, which the top level
+    // reads: stride of its rows, and of digit m-1 inside a row (R^(m-2) padded to lines)
+    int32_t tri, tlo;
+    int32_t swap23;       // 1: its lower digits come in the order x_2, x_3, x_1
+    int64_t trow;
+    int64_t orow, ohi;    // a merge launch's output: stride of its rows, and of the digits
+                          // above its life class
     int32_t R, m, P, nzu, npair, tab, xt, lpmax, dmax, extract;
     int32_t lb[2][10];    // merge block width per [FP32 storage][level j] (0: the LDS rule)
     int32_t exogenous;    // 0: one merge chain per order size a
@@ -258,6 +270,23 @@ hipError_t launch_backup_c(const CDev& p, int storage_fp32, int extract, hipStre
 // digits per workgroup) on the handle's own tables, and write the fastest into lb.  With
 // order-independent life the top level m-1 is timed as it runs, fused with the final sum.
 hipError_t tune_c_merge(const CDev& p, hipStream_t s, int32_t lb[2][10]);
+// Compile-time bound of the antidiagonal kernels' rows for R <= 24, and the entries of one
+// level's packed weights (whole registers of 16).
+inline int c_tri_bound(int R) { return R <= 8 ? 8 : R <= 16 ? 16 : R <= 21 ? 21 : 24; }
+inline size_t c_tri_weights(int R) {
+    const int rc = c_tri_bound(R);
+    return (size_t)((rc * (rc + 1) / 2 + 15) / 16 * 16);
+}
+// The antidiagonal kernels (kernels_ct.hip): the first two merges, the top merge with the
+// final sum (order-independent life), and one order's top merge and final sum.
+template <typename VT>
+bool c_merge23_tri_fits(const CDev& p);
+template <typename VT>
+hipError_t launch_merge23_tri(const CDev& p, const void* u, void* out, hipStream_t s);
+template <typename VT, bool EXTRACT>
+hipError_t launch_c_top(const CDev& p, const void* in, hipStream_t s);
+template <typename VT, bool EXTRACT>
+hipError_t launch_c_order(const CDev& p, const void* in, int a, hipStream_t s);
 // Span partial slots of a scenario-C sweep whose top merge is fused with the final sum
 // (m >= 4, order-independent life): one per workgroup at the narrowest block width, 4
 // of the nlo = R^(m-2) low-digit values, for each of the P weekdays.

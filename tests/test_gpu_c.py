@@ -116,3 +116,27 @@ def test_endogenous_converged(sc):
     res = pvi.vi_solve(m, precision="fp32")
     assert res["final_span"] < res["threshold"]
     assert relerr(vhat(pvi.value_get(m), res, g), vhat(ref["V"], ref, g)) < 1e-5
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("m,a_max,dep", [(4, 3, 0), (4, 7, 1), (4, 8, 0), (4, 15, 1), (4, 20, 0),
+                                         (4, 23, 1), (5, 4, 1), (5, 7, 0), (5, 8, 1), (5, 15, 0),
+                                         (6, 4, 0), (6, 3, 1)])
+def test_antidiagonal_merges_equal_plain(monkeypatch, m, a_max, dep, prec):
+    """Row bounds of 8, 16, 21 and 24 with and without a remainder, few and many rows per
+    phase, order-independent and order-dependent life: the merges by antidiagonals add the
+    plain kernels' terms in their order (PVI_C_BLOCK keeps those), so values, policy and
+    gap are equal bit for bit."""
+    sc = W.scenario_c(m=m, a_max=a_max, d_max=a_max + 3, n=[3.5, 11.0, 7.2, 11.1, 5.9, 5.5, 2.2],
+                      means=[0.3 * a_max + 0.2 * t for t in range(7)],
+                      c0=[0.0] + [1.0 + 0.3 * k for k in range(m - 1)],
+                      c1=[0.0] + [0.05 * dep * (k + 1) for k in range(m - 1)], gamma=0.95)
+    got = []
+    for env in (None, "8"):
+        if env:
+            monkeypatch.setenv("PVI_C_BLOCK", env)
+        h = pvi.mdp_create(sc)
+        pvi.vi_solve(h, precision=prec, fixed_sweeps=3)
+        got.append((pvi.value_get(h),) + pvi.policy_get(h))
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
