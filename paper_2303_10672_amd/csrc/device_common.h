@@ -17,14 +17,30 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
     return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + l;
 }
 
+// Maximum and minimum over a wavefront, the same in every lane: four exchanges inside the
+// rows of 16 lanes (DPP, no LDS), then the four rows' values from the scalar side.  Every
+// lane of the wavefront must be active.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(unsigned)lo | (long long)hi << 32);
+}
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, lane);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double((long long)(unsigned)lo | (long long)hi << 32);
+}
 __device__ __forceinline__ double wave_max(double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
+    v = fmax(v, dpp_f64<0xb1>(v));   // quad_perm: xor 1
+    v = fmax(v, dpp_f64<0x4e>(v));   // quad_perm: xor 2
+    v = fmax(v, dpp_f64<0x141>(v));  // row_half_mirror
+    v = fmax(v, dpp_f64<0x140>(v));  // row_mirror
+    return fmax(fmax(lane_f64(v, 0), lane_f64(v, 16)), fmax(lane_f64(v, 32), lane_f64(v, 48)));
 }
-__device__ __forceinline__ double wave_min(double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-    return v;
-}
+__device__ __forceinline__ double wave_min(double v) { return -wave_max(-v); }
 
 // Block-wide reduction of 4 values (max, min, max, min); result valid in thread 0.
 __device__ inline void block_reduce4(double& a, double& b, double& c, double& d, double* red) {
@@ -93,6 +109,72 @@ __device__ inline void span_update(Ctl& ctl, double a0, double a1, double a2, do
     } else if (crit < ctl.thr) {
         ctl.stop = 1;
         ctl.stop_sweep = ctl.sweeps;
+    }
+}
+
+// ------------------------------------------------------------------ SpanBuf
+__device__ __forceinline__ unsigned long long span_key(double x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    return b >> 63 ? ~b : b | (1ull << 63);
+}
+__device__ __forceinline__ double span_value(unsigned long long k) {
+    return __longlong_as_double((long long)(k >> 63 ? k ^ (1ull << 63) : ~k));
+}
+
+// What a sweep's wavefront reads at its start: the control block as the sweep before left
+// it and the lane's slot of that sweep's keys (requested together, before anything waits).
+struct SpanIn {
+    Ctl ctl;
+    unsigned long long k[4];
+};
+template <bool FP32>
+__device__ __forceinline__ void span_fetch(const SpanBuf* b, int sweep, SpanIn& in) {
+    in.ctl = b->ctl[sweep & 1];
+    const unsigned long long* k = b->key[(sweep + 3) & 3][threadIdx.x & (kSpanSlots - 1)];
+    in.k[0] = k[0];
+    in.k[1] = k[1];
+    if (FP32) {
+        in.k[2] = k[2];
+        in.k[3] = k[3];
+    }
+}
+
+// Applies the sweep before to in.ctl (every lane with the same result).
+template <bool FP32>
+__device__ __forceinline__ void span_reduce(SpanIn& in, int fixed, double gamma) {
+    if (in.ctl.stop || !in.ctl.pending) return;
+    // (a slot nothing was written to decodes to a NaN, which the maxima pass over)
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < (FP32 ? 4 : 2); ++i) v[i] = wave_max(span_value(in.k[i]));
+    span_update(in.ctl, v[0], -v[1], v[2], -v[3], FP32, fixed, gamma);
+}
+
+// The same at a sweep's start, every wavefront for itself; the first workgroup stores it for the next sweep and clears that sweep's keys.  Returns
+// whether the rule has fired; this sweep then does no work.
+template <bool FP32>
+__device__ __forceinline__ bool span_apply(SpanBuf* b, int sweep, SpanIn& in, int fixed,
+                                           double gamma) {
+    span_reduce<FP32>(in, fixed, gamma);
+    in.ctl.pending = !in.ctl.stop;
+    if (blockIdx.x == 0 && threadIdx.x < kSpanSlots) {
+        if (threadIdx.x == 0) b->ctl[(sweep + 1) & 1] = in.ctl;
+        unsigned long long* k = b->key[(sweep + 1) & 3][threadIdx.x];
+        k[0] = k[1] = k[2] = k[3] = 0;
+    }
+    return in.ctl.stop;
+}
+
+// One wavefront's (or workgroup's) increments into the keys of its sweep, by one lane.
+template <bool FP32>
+__device__ __forceinline__ void span_emit(SpanBuf* b, int sweep, int slot, double dmx, double dmn,
+                                          double vmx, double vmn) {
+    unsigned long long* k = b->key[sweep & 3][slot & (kSpanSlots - 1)];
+    __hip_atomic_fetch_max(k, span_key(dmx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_max(k + 1, span_key(-dmn), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (FP32) {
+        __hip_atomic_fetch_max(k + 2, span_key(vmx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_max(k + 3, span_key(-vmn), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 

@@ -642,17 +642,14 @@ void family_free(pvi_mdp* p) {
     d.agroups = nullptr;
 }
 
-// No family fuses the span today: a device-wide release fence per workgroup (needed
-// for a last-workgroup reduction) writes back L2 on every XCD and cost more than
-// the separate single-workgroup span launch it would save.
-bool family_fused_span(const pvi_mdp*) { return false; }
+bool family_fused_span(const pvi_mdp* p) { return p->family == PVI_FAMILY_LEADTIME; }
 
 static hipError_t family_backup_launch(pvi_mdp* p, int fp32, int kahan, int extract, int fixed,
-                                       const void* vin, void* vout, hipStream_t s);
+                                       const void* vin, void* vout, hipStream_t s, int sweep);
 
 hipError_t family_backup(pvi_mdp* p, int fp32, int kahan, int extract, int fixed,
                          const void* vin, void* vout, hipStream_t s, hipEvent_t ev0,
-                         hipEvent_t ev1) {
+                         hipEvent_t ev1, int sweep) {
     if (p->family == PVI_FAMILY_LEADTIME) {
         ADev a = make_adev(p);
         if (!a.lifo) {
@@ -660,24 +657,29 @@ hipError_t family_backup(pvi_mdp* p, int fp32, int kahan, int extract, int fixed
             a.v_in = vin;
             a.v_out = vout;
             a.fixed = fixed;
+            a.span = sweep >= 0 ? p->dev.span : nullptr;
+            a.sweep = sweep;
             return launch_backup_a(a, fp32, kahan, extract, s, ev0, ev1);
         }
     }
     hipError_t e;
     if (ev0 && (e = hipEventRecord(ev0, s)) != hipSuccess) return e;
-    if ((e = family_backup_launch(p, fp32, kahan, extract, fixed, vin, vout, s)) != hipSuccess)
+    if ((e = family_backup_launch(p, fp32, kahan, extract, fixed, vin, vout, s, sweep)) !=
+        hipSuccess)
         return e;
     return ev1 ? hipEventRecord(ev1, s) : hipSuccess;
 }
 
 // The backup of every family other than scenario-A FIFO (that one too, without events).
 static hipError_t family_backup_launch(pvi_mdp* p, int fp32, int kahan, int extract, int fixed,
-                                       const void* vin, void* vout, hipStream_t s) {
+                                       const void* vin, void* vout, hipStream_t s, int sweep) {
     if (p->family == PVI_FAMILY_LEADTIME) {
         ADev a = make_adev(p);
         a.v_in = vin;
         a.v_out = vout;
         a.fixed = fixed;
+        a.span = sweep >= 0 ? p->dev.span : nullptr;
+        a.sweep = sweep;
         if (a.lifo) return launch_backup_a_lifo(a, fp32, extract, s);
         return launch_backup_a(a, fp32, kahan, extract, s, nullptr, nullptr);
     }

@@ -18,10 +18,12 @@ void family_free(pvi_mdp* p);
 // fixed = 1: the sweep belongs to a fixed-length run (no stopping rule).
 hipError_t family_backup(pvi_mdp* p, int fp32, int kahan, int extract, int fixed,
                          const void* vin, void* vout, hipStream_t s, hipEvent_t ev0 = nullptr,
-                         hipEvent_t ev1 = nullptr);  // ev0/ev1: recorded at the backup's start
-                                                     // and end (kernel time), when given
-// True when the family's backup kernel reduces the span itself (its last
-// workgroup applies the stopping rule), so no separate span launch follows it.
+                         hipEvent_t ev1 = nullptr,  // ev0/ev1: recorded at the backup's start
+                                                    // and end (kernel time), when given
+                         int sweep = -1);  // >= 0 (where family_fused_span): number of the
+                                           // sweep in its phase, no span launch follows
+// True when the family's backup can reduce the increments itself (SpanBuf), so that no
+// span launch is needed after each sweep.
 bool family_fused_span(const pvi_mdp* p);
 // Initial values of a family whose paper-defined V0 is not zero (the lead-time-1
 // two-product family: expected one-day revenue), written into v (FP64).

@@ -21,8 +21,8 @@
 //     state of the tile for every action.
 //
 // Wavefront = G tiles (O, X_m..X_3) of one digit sum, R lanes per tile; the tile's
-// path list streams through LDS.  Ties in the max go to the lowest action.  No
-// atomics: every reduction is a fixed tree, so reruns are bit-identical.
+// path list streams through LDS.  Ties in the max go to the lowest action.  Every
+// reduction is a fixed tree or an exact maximum, so reruns are bit-identical.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -157,7 +157,14 @@ __device__ constexpr double kPadValue<double> = -1e300;
 template <typename VT, bool KAHAN, int RMAX, bool EXTRACT, int RC>
 __device__ __forceinline__ void backup_a_body(ADev p, unsigned char* smem) {
     Ctl* ctl = p.ctl;
-    if (!EXTRACT && ctl->stop) return;
+    constexpr bool FP32 = sizeof(VT) == 4;
+    SpanIn si;
+    if constexpr (!EXTRACT) {
+        if (p.span)
+            span_fetch<FP32>(p.span, p.sweep, si);
+        else if (ctl->stop)
+            return;
+    }
     constexpr int W = VecLoad<VT>::W;
     constexpr int SPL = 8;              // actions one staging lane loads
     constexpr int NSPLIT = RMAX / SPL;  // staging lanes per path point
@@ -270,6 +277,12 @@ __device__ __forceinline__ void backup_a_body(ADev p, unsigned char* smem) {
     };
 
     load_chunk(0);
+    double mu = 0.0;
+    if constexpr (!EXTRACT) {
+        // the sweep before is applied while the first chunk is on its way
+        if (p.span && span_apply<FP32>(p.span, p.sweep, si, p.fixed, p.gamma)) return;
+        if (FP32) mu = p.span ? si.ctl.mu : ctl->mu;
+    }
     store_chunk(0);
     wave_sync();
     const int nchunks = (lp + CH - 1) / CH;
@@ -277,7 +290,6 @@ __device__ __forceinline__ void backup_a_body(ADev p, unsigned char* smem) {
 
     const int ns_tile = p.r2 * R;
     const int64_t tbase = (int64_t)tile * ns_tile;
-    const double mu = (!EXTRACT && sizeof(VT) == 4) ? ctl->mu : 0.0;
     const double cv = p.cvar;
     double dmx = -DBL_MAX, dmn = DBL_MAX, vmx = -DBL_MAX, vmn = DBL_MAX;
 
@@ -500,6 +512,14 @@ __device__ __forceinline__ void backup_a_body(ADev p, unsigned char* smem) {
     if (EXTRACT) return;
     dmx = wave_max(dmx);
     dmn = wave_min(dmn);
+    if (p.span) {
+        if (FP32) {
+            vmx = wave_max(vmx);
+            vmn = wave_min(vmn);
+        }
+        if (lane == 0) span_emit<FP32>(p.span, p.sweep, grp, dmx, dmn, vmx, vmn);
+        return;
+    }
     vmx = wave_max(vmx);
     vmn = wave_min(vmn);
     if (lane == 0) {
@@ -565,6 +585,22 @@ __global__ __launch_bounds__(1024) void span_kernel(Ctl* ctl, const double* part
     Ctl next = cur;
     span_update(next, a0, a1, a2, a3, fp32, fixed, gamma);
     *ctl = next;
+}
+
+__global__ __launch_bounds__(256) void span_init_kernel(SpanBuf* b, Ctl first) {
+    if (threadIdx.x == 0) b->ctl[0] = first;
+    unsigned long long* k = &b->key[0][0][0];
+    for (int i = threadIdx.x; i < 4 * kSpanSlots * 4; i += 256) k[i] = 0;
+}
+
+// End of a batch of sweeps 0 .. n - 1: the last one applied, in both copies.
+template <bool FP32>
+__global__ __launch_bounds__(64) void span_end_kernel(SpanBuf* b, int n, int fixed, double gamma) {
+    SpanIn in;
+    span_fetch<FP32>(b, n, in);
+    span_reduce<FP32>(in, fixed, gamma);
+    in.ctl.pending = 0;
+    if (threadIdx.x < 2) b->ctl[threadIdx.x] = in.ctl;
 }
 
 __global__ void to_f64_kernel(const float* v32, double* v64, const Ctl* ctl, int64_t n) {
@@ -652,6 +688,20 @@ hipError_t launch_span(Ctl* ctl, const double* partials, int tiles, int storage_
     const int threads = tiles >= 1024 ? 1024 : tiles <= 64 ? 64 : (tiles + 63) / 64 * 64;
     hipLaunchKernelGGL(span_kernel, dim3(1), dim3(threads), 0, s, ctl, partials, tiles,
                        storage_fp32, fixed, gamma);
+    return hipGetLastError();
+}
+
+hipError_t launch_span_init(SpanBuf* b, const Ctl& first, hipStream_t s) {
+    hipLaunchKernelGGL(span_init_kernel, dim3(1), dim3(256), 0, s, b, first);
+    return hipGetLastError();
+}
+
+hipError_t launch_span_end(SpanBuf* b, int sweeps, int storage_fp32, int fixed, double gamma,
+                           hipStream_t s) {
+    if (storage_fp32)
+        hipLaunchKernelGGL(span_end_kernel<true>, dim3(1), dim3(64), 0, s, b, sweeps, fixed, gamma);
+    else
+        hipLaunchKernelGGL(span_end_kernel<false>, dim3(1), dim3(64), 0, s, b, sweeps, fixed, gamma);
     return hipGetLastError();
 }
 

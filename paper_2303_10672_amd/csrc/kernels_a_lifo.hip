@@ -29,7 +29,14 @@ __global__ __launch_bounds__(1024) void backup_a_lifo_kernel(ADev p) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[64];
     Ctl* ctl = p.ctl;
-    if (!EXTRACT && ctl->stop) return;
+    constexpr bool FP32 = sizeof(VT) == 4;
+    SpanIn si;
+    if constexpr (!EXTRACT) {
+        if (p.span)
+            span_fetch<FP32>(p.span, p.sweep, si);
+        else if (ctl->stop)
+            return;
+    }
     const int R = p.R, m = p.m, tid = threadIdx.x, nt = blockDim.x;
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
     const int h = tile / p.nz, z = tile - h * p.nz;  // z = (X_{m-1}..X_2), X_2 fastest
@@ -73,6 +80,12 @@ __global__ __launch_bounds__(1024) void backup_a_lifo_kernel(ADev p) {
         }
         L[i * R + a] = (double)vin[hbase + (int64_t)a * p.stride_a + off];
     }
+    double mu = 0.0;
+    if constexpr (!EXTRACT) {
+        // every wavefront comes to the same decision
+        if (p.span && span_apply<FP32>(p.span, p.sweep, si, p.fixed, p.gamma)) return;
+        if (FP32) mu = p.span ? si.ctl.mu : ctl->mu;
+    }
     __syncthreads();
     for (int k = tid; k < R * R; k += nt) {
         const int t = k / R, a = k - t * R, K = b + t;
@@ -101,7 +114,6 @@ __global__ __launch_bounds__(1024) void backup_a_lifo_kernel(ADev p) {
     __syncthreads();
     const int64_t base = (int64_t)h * p.stride_h * R + (int64_t)z * R;
     const int64_t tstride = (int64_t)p.pow_y[m - 2] * R;  // R^(m-1): one step of X_m
-    const double mu = (!EXTRACT && sizeof(VT) == 4) ? ctl->mu : 0.0;
     double dmx = -DBL_MAX, dmn = DBL_MAX, vmx = -DBL_MAX, vmn = DBL_MAX;
     for (int k = tid; k < R * R; k += nt) {
         const int t = k / R, x1 = k - t * R;
@@ -121,6 +133,10 @@ __global__ __launch_bounds__(1024) void backup_a_lifo_kernel(ADev p) {
     }
     if (EXTRACT) return;
     block_reduce4(dmx, dmn, vmx, vmn, red);
+    if (p.span) {
+        if (tid == 0) span_emit<FP32>(p.span, p.sweep, tile, dmx, dmn, vmx, vmn);
+        return;
+    }
     if (tid == 0) {
         double* pp = p.partials + 4 * (size_t)tile;
         pp[0] = dmx;

@@ -70,7 +70,8 @@ struct pvi_mdp {
         int32_t* pi = nullptr;
         double* gap = nullptr;
         double* partials = nullptr;
-        pvi::Ctl* ctl = nullptr;
+        pvi::SpanBuf* span = nullptr;
+        pvi::Ctl* ctl = nullptr;  // span->ctl[0]
         pvi::Ctl* h_ctl = nullptr;  // pinned host mirror
         double *pmf = nullptr, *cdf = nullptr, *tail = nullptr, *r0 = nullptr;
         int32_t* agroups = nullptr;
@@ -119,6 +120,17 @@ pvi_status park_results(pvi_mdp* p);
 pvi_status solve_impl(pvi_mdp* p, const pvi_solve_opts* opts, pvi_result* res, bool graphs,
                       std::atomic<int>* progress);
 size_t device_bytes(const pvi_mdp* p);
+// Sweeps to launch before the next host check, from the observed contraction of what the
+// stopping rule tests: max |V' - V| for the sup-norm rule, else the span (which, under
+// discounting, falls below the threshold long before the sup-norm does); the FP32 phase
+// also ends at the span floor.
+struct BatchSizer {
+    int next(const Ctl& h, int k, int kmax, bool fp32);
+
+private:
+    double span_ = -1.0, crit_ = -1.0;
+    int sweeps = 0;
+};
 // Scenario-A work list for G tiles per wavefront and CH path points per staged chunk
 // (0: the default rule); the largest G and CH the kernel takes.
 void build_a_work_list(pvi_mdp* p, int G, int CH);

@@ -17,7 +17,7 @@
 namespace {
 
 // Layout of the scratch array (byte offsets; every region 256-byte aligned).
-constexpr size_t kCtlBytes = 256;
+constexpr size_t kCtlBytes = (sizeof(pvi::SpanBuf) + 255) / 256 * 256;
 constexpr size_t kTableBytes = size_t(512) << 10;     // pmf, cdf, tail, r0, work list
 constexpr size_t kPartialBytes = size_t(512) << 10;   // span partials, 4 doubles each
 constexpr int64_t kMaxStates = int64_t(1) << 22;      // 4,194,304 states
@@ -104,7 +104,8 @@ extern "C" pvi_status vi_solve_noalloc(const pvi_mdp* cp, const pvi_solve_opts* 
     if (st != PVI_OK) return st;
     const auto t0 = std::chrono::steady_clock::now();
     hipStream_t s = (hipStream_t)o.stream;
-    auto* ctl = reinterpret_cast<pvi::Ctl*>(base);
+    auto* span = reinterpret_cast<pvi::SpanBuf*>(base);
+    auto* ctl = reinterpret_cast<pvi::Ctl*>(base);  // span->ctl[0]
     char* tb = base + kCtlBytes;
     auto* partials = reinterpret_cast<double*>(base + kCtlBytes + kTableBytes);
     auto* v_other = reinterpret_cast<double*>(base + kCtlBytes + kTableBytes + kPartialBytes);
@@ -144,42 +145,45 @@ extern "C" pvi_status vi_solve_noalloc(const pvi_mdp* cp, const pvi_solve_opts* 
     h.best_span = INFINITY;
     h.thr = thr;
     h.floor32 = 4.0 * std::ldexp(1.0, -23);
-    PVI_HIP(hipMemcpyAsync(ctl, &h, sizeof(pvi::Ctl), hipMemcpyHostToDevice, s));
+    PVI_HIP(pvi::launch_span_init(span, h, s));
     PVI_HIP(hipStreamSynchronize(s));
 
     const bool fixed = o.fixed_sweeps > 0;
     const int limit = fixed ? o.fixed_sweeps : o.max_sweeps;
     const int kmax = o.check_every > 0 ? o.check_every : 64;
-    auto backup = [&](const double* vin, double* vout, int extract) {
+    auto backup = [&](const double* vin, double* vout, int extract, int sweep) {
         a.v_in = vin;
         a.v_out = vout;
         a.fixed = fixed ? 1 : 0;
+        a.span = extract ? nullptr : span;
+        a.sweep = sweep;
         return a.lifo ? pvi::launch_backup_a_lifo(a, 0, extract, s)
                       : pvi::launch_backup_a(a, 0, 0, extract, s);
     };
-    // batches of direct launches between host checks of the stop flag; launches
-    // after the flag is set return at once, so the batch sizes do not change V
+    // batches of direct launches between host checks of the stop flag, sized like
+    // vi_solve's; launches after the flag is set return at once, so the batch sizes do
+    // not change V
     pvi::Ctl hc{};
+    pvi::BatchSizer sizer;
     int launched = 0, k = 4;
     bool stopped = false;
     while (launched < limit) {
         const int n = std::min(k, limit - launched);
-        for (int i = 0; i < n; ++i, ++launched) {
-            PVI_HIP(backup(slot[launched & 1], slot[(launched + 1) & 1], 0));
-            PVI_HIP(pvi::launch_span(ctl, partials, tiles, 0, fixed ? 1 : 0, g, s));
-        }
+        for (int i = 0; i < n; ++i, ++launched)
+            PVI_HIP(backup(slot[launched & 1], slot[(launched + 1) & 1], 0, launched));
+        PVI_HIP(pvi::launch_span_end(span, launched, 0, fixed ? 1 : 0, g, s));
         PVI_HIP(hipMemcpyAsync(&hc, ctl, sizeof(pvi::Ctl), hipMemcpyDeviceToHost, s));
         PVI_HIP(hipStreamSynchronize(s));
         if (hc.stop) {
             stopped = true;
             break;
         }
-        k = std::min(kmax, 2 * k);
+        k = fixed ? std::min(kmax, 2 * k) : sizer.next(hc, k, kmax, false);
     }
     const int sweeps = hc.sweeps;
     // V after the last sweep that ran is in slot (sweeps & 1): the policy comes from
     // one more FP64 backup of it, and it ends in the caller's table
-    PVI_HIP(backup(slot[sweeps & 1], nullptr, 1));
+    PVI_HIP(backup(slot[sweeps & 1], nullptr, 1, 0));
     if (sweeps & 1)
         PVI_HIP(hipMemcpyAsync(d_v, v_other, sizeof(double) * p->ns, hipMemcpyDeviceToDevice, s));
     PVI_HIP(hipStreamSynchronize(s));

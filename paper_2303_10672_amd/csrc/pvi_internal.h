@@ -25,8 +25,9 @@ pvi_status fail(pvi_status st, const std::string& msg);
     } while (0)
 
 // ------------------------------------------------------------------ device control
-// One per solve, in device memory.  Written only by the single-workgroup span
-// kernel and by the host between launches; read by every backup launch.
+// One per solve, in device memory, read by every backup launch.  Written by the
+// single-workgroup span kernel between the backups, or, where the backup reduces the
+// increments itself (SpanBuf below), by each backup's first workgroup for the next.
 struct Ctl {
     double mu;        // FP32 storage: centre shift applied to the next sweep
     double c;         // FP32 storage: FP64 offset of the current iterate, V = c + v
@@ -43,8 +44,25 @@ struct Ctl {
     int32_t fp32_phase;
     int32_t rule;     // 0: span rule, 1: sup-norm rule max|V_new - V| < thr,
                       // 2: periodic rule (decided by the periodic check kernels)
-    int32_t pad[2];
+    int32_t pending;  // SpanBuf: the last sweep's increments are not yet applied
+    int32_t pad;
 };
+
+// Control block of a solve whose backups need no span launch between them.  Sweep i
+// reduces its increments into the keys of set i % 4 (atomic maxima of an order-preserving
+// image of the doubles, spread over kSpanSlots slots: exact and independent of the order);
+// sweep i + 1 reads that set at its start, and every workgroup applies the stopping rule
+// to its own copy of ctl[(i + 1) % 2], which the first one stores as ctl[i % 2] for sweep
+// i + 2.  Sweep i also clears set i + 1.  A launch at the end of each batch applies the
+// last sweep and leaves the result in both copies.
+constexpr int kSpanSlots = 64;
+struct SpanBuf {
+    Ctl ctl[2];
+    alignas(128) unsigned long long key[4][kSpanSlots][4];  // max dv, -min dv, max v', -min v'
+};
+hipError_t launch_span_init(SpanBuf* b, const Ctl& first, hipStream_t s);
+hipError_t launch_span_end(SpanBuf* b, int sweeps, int storage_fp32, int fixed, double gamma,
+                           hipStream_t s);
 
 // ------------------------------------------------------------------ family A
 struct ADev {
@@ -58,6 +76,8 @@ struct ADev {
     const double* cdf;  // [tab]: P(D <= d), one beyond d_max
     const double* tail; // [tab]: P(D >= d), zero beyond d_max
     Ctl* ctl;
+    SpanBuf* span;      // not null: no span launch follows this sweep, number `sweep`
+    int32_t sweep;
     int64_t stride_a;   // R^(m+L-2): offset of next-state block of action a
     int64_t stride_h;   // R^(m-1): block size, one block per in-transit vector
     int32_t R, m, dmax, xt, tab;

@@ -20,7 +20,7 @@ size_t device_bytes(const pvi_mdp* p) {
     const size_t ns = (size_t)p->ns;
     size_t b = ns * (2 * sizeof(double) + 2 * sizeof(float) + sizeof(int32_t) + sizeof(double));
     b += family_extra_bytes(p);
-    b += 4 * sizeof(double) * (size_t)family_tiles(p) + sizeof(Ctl) + 4096;
+    b += 4 * sizeof(double) * (size_t)family_tiles(p) + sizeof(SpanBuf) + 4096;
     // value tables the periodic stopping rule keeps beyond the two ping-pong ones
     if (p->P > 1) b += sizeof(double) * ((size_t)(p->P - 1) * ns + 2 * kPeriodicBlocks);
     return b;
@@ -34,7 +34,7 @@ void free_device(pvi_mdp* p) {
     (void)hipSetDevice(d.device);
     if (d.own) (void)hipStreamSynchronize(d.own);
     void* bufs[] = {d.v64[0], d.v64[1], d.v32[0], d.v32[1], d.pi,  d.gap,
-                    d.partials, d.ctl, d.pmf,   d.cdf,   d.tail, d.r0};
+                    d.partials, d.span, d.pmf,   d.cdf,   d.tail, d.r0};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     for (double*& b : d.vring)
@@ -97,7 +97,8 @@ pvi_status ensure_device(pvi_mdp* p) {
               alloc((void**)&d.pi, ns * 4) && alloc((void**)&d.gap, ns * 8);
     d.tiles = family_tiles(p);
     ok = ok && alloc((void**)&d.partials, 4 * sizeof(double) * (size_t)d.tiles) &&
-         alloc((void**)&d.ctl, sizeof(Ctl));
+         alloc((void**)&d.span, sizeof(SpanBuf));
+    d.ctl = reinterpret_cast<Ctl*>(d.span);
     if (ok && p->family == PVI_FAMILY_LEADTIME) {
         ok = upload(&d.pmf, p->a_pmf) == hipSuccess && upload(&d.cdf, p->a_cdf) == hipSuccess &&
              upload(&d.tail, p->a_tail) == hipSuccess && upload(&d.r0, p->a_r0) == hipSuccess;
@@ -203,12 +204,12 @@ pvi_status init_ctl(pvi_mdp* p, hipStream_t s, double thr, double c0, int rule) 
     h.thr = thr;
     h.floor32 = 4.0 * std::ldexp(1.0, -23);
     *p->dev.h_ctl = h;
-    PVI_HIP(hipMemcpyAsync(p->dev.ctl, p->dev.h_ctl, sizeof(Ctl), hipMemcpyHostToDevice, s));
+    PVI_HIP(launch_span_init(p->dev.span, h, s));
     return PVI_OK;
 }
 
-// Sweeps per captured graph: an even number, so every replay starts on the same
-// ping-pong table.
+// Sweeps per captured graph: a multiple of four, so every replay starts on the same
+// ping-pong table and set of increment keys.
 constexpr int kGraphSweeps = 8;
 
 // Launch the backup and span kernels of sweep `launched` (ping-pong tables; no
@@ -217,14 +218,16 @@ pvi_status launch_sweep(pvi_mdp* p, const Phase& ph, int launched, hipStream_t s
     auto& d = p->dev;
     const void* vin = ph.fp32 ? (const void*)d.v32[launched & 1] : v64_slot(p, launched & 1);
     void* vout = ph.fp32 ? (void*)d.v32[(launched + 1) & 1] : v64_slot(p, (launched + 1) & 1);
-    PVI_HIP(family_backup(p, ph.fp32, ph.kahan, 0, ph.fixed > 0, vin, vout, s));
-    if (!family_fused_span(p))
+    const bool fused = family_fused_span(p);
+    PVI_HIP(family_backup(p, ph.fp32, ph.kahan, 0, ph.fixed > 0, vin, vout, s, nullptr, nullptr,
+                          fused ? launched : -1));
+    if (!fused)
         PVI_HIP(launch_span(d.ctl, d.partials, d.tiles, ph.fp32 ? 1 : 0, ph.fixed > 0,
                             p->d.gamma, s));
     return PVI_OK;
 }
 
-// The instantiated graph of kGraphSweeps sweeps from an even sweep index, captured
+// The instantiated graph of kGraphSweeps sweeps from a multiple of four, captured
 // on stream s at first use.  Each sweep's launches read the device stop flag, so a
 // replay after the stopping rule fired does no work; the host still checks the flag
 // between replays, as between batches of direct launches.
@@ -258,8 +261,8 @@ pvi_status sweep_graph(pvi_mdp* p, const Phase& ph, hipStream_t s, hipGraphExec_
 pvi_status run_phase(pvi_mdp* p, const Phase& ph, hipStream_t s, PhaseOut& out) {
     auto& d = p->dev;
     int launched = 0, k = ph.k0;
-    double prev_span = -1.0, prev_crit = -1.0;
-    int prev_sweeps = 0, last_ckpt = 0;
+    BatchSizer sizer;
+    int last_ckpt = 0;
     const int limit = ph.fixed > 0 ? ph.fixed : ph.max_sweeps;
     if (ph.time && (int)d.ev.size() < 2 * ph.kmax) {
         // timing only: no system-scope fence when they complete (the control block
@@ -273,43 +276,50 @@ pvi_status run_phase(pvi_mdp* p, const Phase& ph, hipStream_t s, PhaseOut& out) 
     // graphs serve the plain ping-pong loop; timed runs and the periodic rule (whose
     // value tables rotate through a longer ring) launch directly
     const bool graphs = ph.graphs && !ph.time && ph.period == 0 && ph.ring == 2;
+    // without a span launch per sweep: the periodic test reads the control block between
+    // the sweeps, so it keeps them
+    const bool fused = family_fused_span(p) && ph.period == 0;
     while (launched < limit) {
-        int n = std::min(k, limit - launched);
+        const int n = std::min(k, limit - launched), end = launched + n;
         const int before = d.h_ctl->sweeps;
-        if (graphs && (launched & 1) == 0 && n >= kGraphSweeps) {
-            n -= n % kGraphSweeps;
-            hipGraphExec_t exec = nullptr;
-            const pvi_status st = sweep_graph(p, ph, s, &exec);
-            if (st != PVI_OK) return st;
-            for (int i = 0; i < n; i += kGraphSweeps) PVI_HIP(hipGraphLaunch(exec, s));
-            launched += n;
-        } else {
-            for (int i = 0; i < n; ++i) {
-                const void* vin = ph.fp32 ? (const void*)d.v32[launched & 1]
-                                          : v64_slot(p, ring_slot(launched, 0, ph.ring));
-                void* vout = ph.fp32 ? (void*)d.v32[(launched + 1) & 1]
-                                     : v64_slot(p, ring_slot(launched + 1, 0, ph.ring));
-                PVI_HIP(family_backup(p, ph.fp32, ph.kahan, 0, ph.fixed > 0, vin, vout, s,
-                                      ph.time ? d.ev[2 * i] : nullptr,
-                                      ph.time ? d.ev[2 * i + 1] : nullptr));
-                if (!family_fused_span(p))
-                    PVI_HIP(launch_span(d.ctl, d.partials, d.tiles, ph.fp32 ? 1 : 0,
-                                        ph.fixed > 0, p->d.gamma, s));
-                ++launched;
-                if (ph.period > 0 && launched + ph.hist0 >= ph.period) {
-                    // V_{i-j} for j = 0..P, i = launched (a sweep that was skipped after
-                    // the stop flag leaves its table untouched, and so does this check)
-                    PeriodicArgs a{};
-                    for (int j = 0; j <= ph.period; ++j)
-                        a.v[j] = v64_slot(p, ring_slot(launched, j, ph.ring));
-                    a.P = ph.period;
-                    a.gamma = ph.gamma;
-                    a.thr = ph.thr;
-                    a.n = p->ns;
-                    PVI_HIP(launch_periodic_check(d.ctl, a, d.pparts, s));
-                }
+        int direct = 0;  // launched one by one (timing events are theirs)
+        while (launched < end) {
+            if (graphs && (launched & 3) == 0 && end - launched >= kGraphSweeps) {
+                hipGraphExec_t exec = nullptr;
+                const pvi_status st = sweep_graph(p, ph, s, &exec);
+                if (st != PVI_OK) return st;
+                PVI_HIP(hipGraphLaunch(exec, s));
+                launched += kGraphSweeps;
+                continue;
+            }
+            const void* vin = ph.fp32 ? (const void*)d.v32[launched & 1]
+                                      : v64_slot(p, ring_slot(launched, 0, ph.ring));
+            void* vout = ph.fp32 ? (void*)d.v32[(launched + 1) & 1]
+                                 : v64_slot(p, ring_slot(launched + 1, 0, ph.ring));
+            PVI_HIP(family_backup(p, ph.fp32, ph.kahan, 0, ph.fixed > 0, vin, vout, s,
+                                  ph.time ? d.ev[2 * direct] : nullptr,
+                                  ph.time ? d.ev[2 * direct + 1] : nullptr,
+                                  fused ? launched : -1));
+            if (!fused)
+                PVI_HIP(launch_span(d.ctl, d.partials, d.tiles, ph.fp32 ? 1 : 0, ph.fixed > 0,
+                                    p->d.gamma, s));
+            ++direct;
+            ++launched;
+            if (ph.period > 0 && launched + ph.hist0 >= ph.period) {
+                // V_{i-j} for j = 0..P, i = launched (a sweep that was skipped after
+                // the stop flag leaves its table untouched, and so does this check)
+                PeriodicArgs a{};
+                for (int j = 0; j <= ph.period; ++j)
+                    a.v[j] = v64_slot(p, ring_slot(launched, j, ph.ring));
+                a.P = ph.period;
+                a.gamma = ph.gamma;
+                a.thr = ph.thr;
+                a.n = p->ns;
+                PVI_HIP(launch_periodic_check(d.ctl, a, d.pparts, s));
             }
         }
+        if (fused)
+            PVI_HIP(launch_span_end(d.span, launched, ph.fp32 ? 1 : 0, ph.fixed > 0, p->d.gamma, s));
         PVI_HIP(hipMemcpyAsync(d.h_ctl, d.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
         PVI_HIP(hipStreamSynchronize(s));
         const Ctl& h = *d.h_ctl;
@@ -332,31 +342,7 @@ pvi_status run_phase(pvi_mdp* p, const Phase& ph, hipStream_t s, PhaseOut& out) 
             if (st != PVI_OK) return st;
             last_ckpt = h.sweeps;
         }
-        // size the next batch from the observed contraction of what the stopping rule
-        // tests: max |V' - V| for the sup-norm rule, else the span (which, under
-        // discounting, falls below the threshold long before the sup-norm does); the
-        // FP32 phase also ends at the span floor
-        const double crit = h.rule == 1 ? std::max(std::fabs(h.dmax), std::fabs(h.dmin)) : h.span;
-        const int gap = h.sweeps - prev_sweeps;
-        if (ph.fixed > 0) {
-            k = std::min(ph.kmax, 2 * k);
-        } else if (prev_crit > 0.0 && crit > 0.0 && crit < prev_crit && gap > 0) {
-            const double rate = std::pow(crit / prev_crit, 1.0 / gap);
-            // a threshold <= 0 never stops the solve: full batches
-            double need =
-                rate < 1.0 && h.thr > 0.0 ? std::log(h.thr / crit) / std::log(rate) : ph.kmax;
-            if (ph.fp32 && prev_span > 0.0 && h.span > 0.0 && h.span < prev_span) {
-                const double rs = std::pow(h.span / prev_span, 1.0 / gap);
-                if (rs < 1.0)
-                    need = std::min(need, std::log(h.floor32 * h.vabs / h.span) / std::log(rs));
-            }
-            k = (int)std::min<double>(ph.kmax, std::max(1.0, std::ceil(need)));
-        } else {
-            k = std::min(ph.kmax, 2 * k);
-        }
-        prev_span = h.span;
-        prev_crit = crit;
-        prev_sweeps = h.sweeps;
+        k = ph.fixed > 0 ? std::min(ph.kmax, 2 * k) : sizer.next(h, k, ph.kmax, ph.fp32);
     }
     out.sweeps = d.h_ctl->sweeps;
     return PVI_OK;
@@ -373,6 +359,29 @@ double midrange(const double* v, int64_t n) {
 }
 
 }  // namespace
+
+int BatchSizer::next(const Ctl& h, int k, int kmax, bool fp32) {
+    const double crit = h.rule == 1 ? std::max(std::fabs(h.dmax), std::fabs(h.dmin)) : h.span;
+    const int gap = h.sweeps - sweeps;
+    if (crit_ > 0.0 && crit > 0.0 && crit < crit_ && gap > 0) {
+        const double rate = std::pow(crit / crit_, 1.0 / gap);
+        // a threshold <= 0 never stops the solve: full batches
+        double need = rate < 1.0 && h.thr > 0.0 ? std::log(h.thr / crit) / std::log(rate) : kmax;
+        if (fp32 && span_ > 0.0 && h.span > 0.0 && h.span < span_) {
+            const double rs = std::pow(h.span / span_, 1.0 / gap);
+            if (rs < 1.0)
+                need = std::min(need, std::log(h.floor32 * h.vabs / h.span) / std::log(rs));
+        }
+        k = (int)std::min<double>(kmax, std::max(1.0, std::ceil(need)));
+    } else {
+        k = std::min(kmax, 2 * k);
+    }
+    span_ = h.span;
+    crit_ = crit;
+    sweeps = h.sweeps;
+    return k;
+}
+
 // Move the results of the last solve (V, policy, Q gap) into the handle's host
 // vectors and give its device buffers back.  The request server calls this for
 // handles whose device state its own request created, so completed requests do
@@ -600,15 +609,13 @@ pvi_status vi_backup(pvi_mdp* p, int32_t precision, const double* v_in, double* 
     if (precision == PVI_FP64) {
         if ((st = init_ctl(p, s, -1.0, 0.0, PVI_STOP_SPAN)) != PVI_OK) return st;
         PVI_HIP(family_backup(p, 0, 0, 0, 1, d.v64[0], d.v64[1], s));
-        if (!family_fused_span(p))
-            PVI_HIP(launch_span(d.ctl, d.partials, d.tiles, 0, 1, p->d.gamma, s));
+        PVI_HIP(launch_span(d.ctl, d.partials, d.tiles, 0, 1, p->d.gamma, s));
     } else {
         const double c0 = midrange(v_in, p->ns);
         PVI_HIP(launch_to_f32(d.v64[0], d.v32[0], c0, p->ns, s));
         if ((st = init_ctl(p, s, -1.0, c0, PVI_STOP_SPAN)) != PVI_OK) return st;
         PVI_HIP(family_backup(p, 1, precision == PVI_FP32, 0, 1, d.v32[0], d.v32[1], s));
-        if (!family_fused_span(p))
-            PVI_HIP(launch_span(d.ctl, d.partials, d.tiles, 1, 1, p->d.gamma, s));
+        PVI_HIP(launch_span(d.ctl, d.partials, d.tiles, 1, 1, p->d.gamma, s));
         PVI_HIP(launch_to_f64(d.v32[1], d.v64[1], d.ctl, p->ns, s));
     }
     PVI_HIP(family_backup(p, 0, 0, 1, 0, d.v64[0], nullptr, s));

@@ -55,3 +55,32 @@ def test_fixed_sweeps_through_graphs():
         b = pvi.vi_solve(m, precision="fp64", fixed_sweeps=n, time_kernels=True)
         assert a["sweeps_fp64"] == b["sweeps_fp64"] == n
         assert np.array_equal(Va, pvi.value_get(m))
+
+
+@pytest.mark.parametrize("sc", [W.scenario_a(m=2, L=1, a_max=6, d_max=15),
+                                W.scenario_a(m=3, L=2, a_max=10, d_max=25),
+                                W.scenario_a(m=4, L=1, a_max=10, d_max=25, issuing="lifo"),
+                                W.scenario_a(m=2, L=1, a_max=9, d_max=15, issuing="lifo")],
+                         ids=["one-group", "many-groups", "lifo-many", "lifo"])
+def test_increments_reduced_by_the_backups(sc):
+    """Backups that reduce the increments themselves against single backups followed by a
+    span launch: values, largest and smallest increment after every sweep count up to two
+    graphs and a remainder, and the sweep at which each rule fires."""
+    m = pvi.mdp_create(sc)
+    v, incr = np.zeros(m.n_states), []
+    for k in range(1, 20):
+        new, _, _ = pvi.vi_backup(m, v)
+        incr.append((np.max(new - v), np.min(new - v)))
+        v = new
+        r = pvi.vi_solve(m, precision="fp64", fixed_sweeps=k)
+        assert np.array_equal(pvi.value_get(m), v)
+        assert (r["dmax"], r["dmin"]) == incr[-1]
+    for rule, size in (("span", lambda x: x[0] - x[1]),
+                       ("supnorm", lambda x: max(abs(x[0]), abs(x[1])))):
+        for k in (3, 9, 14):
+            eps = size(incr[k]) * 1.0000001  # first met at sweep k + 1 (the sizes fall)
+            first = next(i for i, x in enumerate(incr) if size(x) < eps) + 1
+            g = sc["gamma"]
+            r = pvi.vi_solve(m, precision="fp64", stop_rule=rule,
+                             eps=eps * g / (1 - g) if rule == "span" else eps)
+            assert r["sweeps_fp64"] == first
