@@ -229,11 +229,20 @@ struct SimDev {
     const double* cdf0;        // [P][dmax0 + 1] demand CDF of product 0, summed left to right
     const double* cdf1;        // [dmax1 + 1] demand CDF of product 1 (B)
     const double* lifecum;     // C: [a_max + 1][m], p_1(a) + ... + p_k(a) at a*m + k-1
+    // the numbers drawn ahead, [day][rollout] (dem null: drawn day by day): both demands,
+    // acceptances of substitution, and scenario C's [m] words of remaining life per unit
+    uint32_t* dem;
+    uint64_t* bits;
+    uint32_t* life;
+    int32_t tau0, by_block;    // weekday of day 0; workgroups of one policy each
+    int32_t pw0[24], pw1[8];   // state index weights of product 0's digits (scenario A: then
+                               // the orders; C: then the weekday) and of product 1's
     double* ret;               // [n_pol * n_roll]
     double* kpi;               // [n_pol * n_roll][3]
     double* pkpi;              // two products: [n_pol * n_roll][2][3], or null
 };
 hipError_t launch_rollouts(const SimDev& s, hipStream_t st);
+hipError_t launch_draws(const SimDev& s, hipStream_t st);
 // Mean and sample standard deviation of ncol columns of x ([n_pol][n_roll][stride],
 // column c at offset c), written to out[p * ostride + ooff + 2 c] and the next slot.
 hipError_t launch_column_stats(const double* x, int stride, int ncol, int n_pol, int n_roll,

@@ -4,6 +4,7 @@
 // heuristic_search.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstddef>
 #include <cstring>
@@ -27,15 +28,45 @@ struct SimBuffers {
         }
         for (void* q : ptrs) (void)hipFree(q);
     }
+    // pieces of one device allocation: each is asked for, then all are taken at once
+    struct Piece {
+        void** out;
+        size_t off;
+    };
+    std::vector<Piece> pieces;
+    size_t bytes = 0;
     template <class T>
-    hipError_t alloc(T** out, size_t n) {
+    void want(T** out, size_t n) {
+        pieces.push_back({reinterpret_cast<void**>(out), bytes});
+        bytes += (sizeof(T) * std::max<size_t>(n, 1) + 255) & ~size_t(255);
+    }
+    hipError_t take() {
         void* q = nullptr;
-        hipError_t e = hipMalloc(&q, sizeof(T) * std::max<size_t>(n, 1));
-        if (e == hipSuccess) ptrs.push_back(q);
-        *out = static_cast<T*>(q);
+        const hipError_t e = hipMalloc(&q, bytes);
+        if (e == hipSuccess) {
+            ptrs.push_back(q);
+            for (const Piece& w : pieces) *w.out = static_cast<char*>(q) + w.off;
+        } else {
+            (void)hipGetLastError();
+        }
+        pieces.clear();
+        bytes = 0;
         return e;
     }
 };
+
+// Whether every order has the same remaining-life distribution, so that a unit's life can
+// be drawn before its order is known (an order of 0 draws none).
+bool one_life_row(const std::vector<double>& lcum, int rows, int m) {
+    for (int a = 2; a < rows; ++a)
+        for (int k = 0; k < m - 1; ++k)
+            if (lcum[(size_t)a * m + k] != lcum[(size_t)m + k]) return false;
+    return true;
+}
+
+// Numbers drawn ahead take at most this much device memory; a call that needs more draws
+// them day by day.
+constexpr int64_t kDrawBytes = int64_t(1) << 30;
 
 pvi_status check_kind(const pvi_mdp* p, int kind) {
     if (kind == PVI_POLICY_TABLE) return PVI_OK;
@@ -117,20 +148,25 @@ pvi_status run_rollouts(pvi_mdp* p, const pvi_rollout_opts* o, double* stats, do
     if (!two && (pkpis || pstats))
         return fail(PVI_E_INVALID, w + ": per-product KPIs need a two-product family");
     const int R0 = p->rad[0], R1 = two ? p->rad[1] : 1;
-    // demand CDFs, summed left to right over the PMF of each period
+    // demand CDFs, summed left to right over the PMF of each period, as running maxima: the
+    // first d with u below the sums is then the first of a sequence that never falls (a
+    // difference of rounded gamma CDFs may be negative by an ulp), which halving finds
     const int P = p->family == PVI_FAMILY_RUL_WEEKDAY ? p->P : 1;
     std::vector<double> cdf0((size_t)P * (p->dmax[0] + 1)), cdf1;
     for (int t = 0; t < P; ++t) {
-        double c = 0.0;
+        double c = 0.0, top = 0.0;
         for (int d = 0; d <= p->dmax[0]; ++d) {
             c += p->pmf[0][(size_t)t * (p->dmax[0] + 1) + d];
-            cdf0[(size_t)t * (p->dmax[0] + 1) + d] = c;
+            cdf0[(size_t)t * (p->dmax[0] + 1) + d] = top = std::max(top, c);
         }
     }
     if (two) {
         cdf1.resize(p->dmax[1] + 1);
-        double c = 0.0;
-        for (int d = 0; d <= p->dmax[1]; ++d) cdf1[d] = c += p->pmf[1][d];
+        double c = 0.0, top = 0.0;
+        for (int d = 0; d <= p->dmax[1]; ++d) {
+            c += p->pmf[1][d];
+            cdf1[d] = top = std::max(top, c);
+        }
     }
     std::vector<double> lcum;
     if (p->family == PVI_FAMILY_RUL_WEEKDAY) {
@@ -208,38 +244,72 @@ pvi_status run_rollouts(pvi_mdp* p, const pvi_rollout_opts* o, double* stats, do
 
     const size_t lanes = (size_t)n_pol * o->n_rollouts;
     const bool split = pkpis || pstats;
-    double *dc0, *dc1, *dlc, *dret, *dkpi, *dstats, *dpkpi = nullptr, *dpstats = nullptr;
+    // the three staged tables lie in one piece and go up in one copy
+    std::vector<double> tabs(cdf0);
+    tabs.insert(tabs.end(), cdf1.begin(), cdf1.end());
+    tabs.insert(tabs.end(), lcum.begin(), lcum.end());
+    double *dtabs, *dret, *dkpi, *dstats, *dpkpi = nullptr, *dpstats = nullptr;
     int32_t *dprm = nullptr, *dtab = nullptr;
-    if (B.alloc(&dc0, cdf0.size()) != hipSuccess || B.alloc(&dc1, cdf1.size()) != hipSuccess ||
-        B.alloc(&dlc, lcum.size()) != hipSuccess || B.alloc(&dret, lanes) != hipSuccess ||
-        B.alloc(&dkpi, 3 * lanes) != hipSuccess || B.alloc(&dstats, 8 * (size_t)n_pol) != hipSuccess)
-        return fail(PVI_E_NOMEM, w + ": device allocation failed");
-    if (split && (B.alloc(&dpkpi, 6 * lanes) != hipSuccess ||
-                  B.alloc(&dpstats, 12 * (size_t)n_pol) != hipSuccess))
-        return fail(PVI_E_NOMEM, w + ": device allocation failed");
-    PVI_HIP(hipMemcpyAsync(dc0, cdf0.data(), sizeof(double) * cdf0.size(), hipMemcpyHostToDevice, s));
-    if (!cdf1.empty())
-        PVI_HIP(hipMemcpyAsync(dc1, cdf1.data(), sizeof(double) * cdf1.size(), hipMemcpyHostToDevice, s));
-    if (!lcum.empty())
-        PVI_HIP(hipMemcpyAsync(dlc, lcum.data(), sizeof(double) * lcum.size(), hipMemcpyHostToDevice, s));
-    if (o->kind != PVI_POLICY_TABLE) {
-        if (B.alloc(&dprm, (size_t)n_pol * PVI_POLICY_PARAMS) != hipSuccess)
-            return fail(PVI_E_NOMEM, w + ": device allocation failed");
+    B.want(&dtabs, tabs.size());
+    B.want(&dret, lanes);
+    B.want(&dkpi, 3 * lanes);
+    B.want(&dstats, 8 * (size_t)n_pol);
+    if (split) {
+        B.want(&dpkpi, 6 * lanes);
+        B.want(&dpstats, 12 * (size_t)n_pol);
+    }
+    if (o->kind != PVI_POLICY_TABLE)
+        B.want(&dprm, (size_t)n_pol * PVI_POLICY_PARAMS);
+    else if (!dtab_src)
+        B.want(&dtab, (size_t)p->ns);
+    if (B.take() != hipSuccess) return fail(PVI_E_NOMEM, w + ": device allocation failed");
+    // The day's numbers can be drawn before the policies run where a unit's draw does not
+    // depend on the order: its life (scenario C) then has one distribution.  Units are bits
+    // of a word: at most 64 customers of substitution (an order has at most 31 units).
+    const int64_t n_draw = (int64_t)o->n_rollouts * ((int64_t)o->warmup_days + o->horizon_days);
+    const int units = d.family == 1 ? d.dmax0 : d.family == 3 ? d.dmax1 : 0;
+    const int64_t draw_bytes =
+        n_draw * (int64_t)(sizeof(uint32_t) + (two ? sizeof(uint64_t) : 0) +
+                           (d.family == 2 ? sizeof(uint32_t) * p->m : 0));
+    bool ahead = draw_bytes <= kDrawBytes && d.dmax0 < 65536 && d.dmax1 < 65536 && units <= 64;
+    if (d.family == 2) ahead = ahead && one_life_row(lcum, R0, p->m);
+    if (ahead) {
+        B.want(&d.dem, n_draw);
+        if (two) B.want(&d.bits, n_draw);
+        if (d.family == 2) B.want(&d.life, n_draw * p->m);
+        if (B.take() != hipSuccess) d.dem = nullptr;  // no room: drawn day by day
+    }
+    PVI_HIP(hipMemcpyAsync(dtabs, tabs.data(), sizeof(double) * tabs.size(),
+                           hipMemcpyHostToDevice, s));
+    if (o->kind != PVI_POLICY_TABLE)
         PVI_HIP(hipMemcpyAsync(dprm, o->params, sizeof(int32_t) * n_pol * PVI_POLICY_PARAMS,
                                hipMemcpyHostToDevice, s));
-    } else if (!dtab_src) {
-        if (B.alloc(&dtab, (size_t)p->ns) != hipSuccess)
-            return fail(PVI_E_NOMEM, w + ": device allocation failed");
+    else if (!dtab_src)
         PVI_HIP(hipMemcpyAsync(dtab, htab.data(), sizeof(int32_t) * p->ns, hipMemcpyHostToDevice, s));
-    }
     d.table = dtab_src ? dtab_src : dtab;
     d.params = dprm;
-    d.cdf0 = dc0;
-    d.cdf1 = dc1;
-    d.lifecum = dlc;
+    d.cdf0 = dtabs;
+    d.cdf1 = dtabs + cdf0.size();
+    d.lifecum = dtabs + cdf0.size() + cdf1.size();
     d.ret = dret;
     d.kpi = dkpi;
     d.pkpi = dpkpi;
+    if (o->kind == PVI_POLICY_TABLE) {  // at most 2^31 states: the weights fit
+        const int n0 = d.family == 0 ? p->m + p->L - 1 : d.family == 3 ? p->m : p->m - 1;
+        int64_t at = 1;
+        if (two)
+            for (int j = 0; j < n0; ++j, at *= R1) d.pw1[j] = (int32_t)at;
+        for (int j = 0; j < n0; ++j, at *= R0) d.pw0[j] = (int32_t)at;
+        if (d.family == 2) d.pw0[n0] = (int32_t)at;
+    }
+    if (d.family == 2) {
+        int64_t per = 1;
+        for (int j = 0; j < p->m - 1; ++j) per *= R0;
+        d.tau0 = (int32_t)(o->start_state / per);
+    }
+    // Policies of 64 rollouts side by side, where whole workgroups leave few lanes idle
+    d.by_block = (int64_t)((d.n_roll + 63) / 64) * 64 <= (int64_t)d.n_roll + d.n_roll / 8;
+    if (d.dem) PVI_HIP(launch_draws(d, s));
     PVI_HIP(launch_rollouts(d, s));
     // stats[p] = (return, service, wastage, holding) x (mean, sd)
     PVI_HIP(launch_column_stats(dret, 1, 1, n_pol, o->n_rollouts, dstats, 8, 0, s));

@@ -152,6 +152,46 @@ def test_large_table_and_base_stock_at_the_largest_preset():
     _same(g, o.simulate("base_stock", params=grid, n_rollouts=100, seed=2))
 
 
+# On each side of the widths of a day's numbers drawn ahead (64 customers; 31 units ordered, the most there are)
+# and in each compiled life and the general one
+DRAWN = {
+    "A-m1-L2": (W.scenario_a(m=1, L=2, a_max=6, d_max=9), "base_stock", [[5], [9]]),
+    "A-m2": (W.scenario_a(m=2, L=1, a_max=6, d_max=9), "base_stock", [[S] for S in range(5)]),
+    "A-m6-L3": (W.scenario_a(m=6, L=3, a_max=2, d_max=6), "base_stock", [[3], [0], [9]]),
+    "A-m3-L2-lifo": (W.scenario_a(m=3, L=2, a_max=5, d_max=9, issuing="lifo"), "base_stock",
+                     [[4], [8]]),
+    "B-64": (W.scenario_b(m=2, a_max=(4, 31), d_max=(64, 8), means=(62.0, 3.0)),
+             "mod_base_stock", [[4, 31], [0, 60], [2, 90]]),
+    "B-65": (W.scenario_b(m=2, a_max=(4, 31), d_max=(65, 8), means=(64.0, 3.0)),
+             "mod_base_stock", [[4, 31], [0, 60], [2, 90]]),
+    "B-m4": (W.scenario_b(m=4, a_max=(3, 3), d_max=(6, 6), means=(3.0, 2.0)),
+             "mod_base_stock", [[4, 3], [2, 9]]),
+    "B1-64": (W.scenario_b1(m=3, a_max=(6, 2), means=(1.0, 62.0), d_max=64), "mod_base_stock",
+              [[60, 2], [90, 0]]),
+    "B1-65": (W.scenario_b1(m=2, a_max=(6, 2), means=(1.0, 64.0), d_max=65), "mod_base_stock",
+              [[60, 2], [90, 0]]),
+    "C-31": (W.scenario_c(m=3, a_max=31, d_max=30, c0=[0.0, 1.0, 0.5]), "s_S",
+             [[20, 31] * 7, [31, 62] * 7]),
+    "C-m6": (W.scenario_c(m=6, a_max=2, d_max=4, c0=[0.0, 1.0, 0.5, 0.2, 0.9, 0.1]), "s_S",
+             [[1, 2] * 7, [2, 4] * 7]),
+}
+
+
+@pytest.mark.parametrize("n_rollouts", [1, 64, 65, 130])
+@pytest.mark.parametrize("name", list(DRAWN))
+def test_numbers_drawn_ahead_match_oracle(name, n_rollouts):
+    sc, kind, grid = DRAWN[name]
+    o = Oracle(sc)
+    m = pvi.mdp_create(sc)
+    rng = np.random.default_rng([21, n_rollouts])
+    table = rng.integers(0, o.n_actions, size=o.n_states).astype(np.int32)
+    run = dict(n_rollouts=n_rollouts, warmup=3, horizon=25, seed=2 ** 63 + 5,
+               start=o.n_states - 1)
+    _same(pvi.policy_rollouts(m, table=table, **run), o.simulate("table", table=table, **run))
+    _same(pvi.policy_rollouts(m, policy=kind, params=grid, **run),
+          o.simulate(kind, params=grid, **run))
+
+
 def _close(ours, printed, sd, digits=0):
     return abs(ours - printed) <= 4.0 * sd * np.sqrt(2.0 / 10000) + 0.5 * 10.0 ** -digits
 
