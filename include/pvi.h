@@ -60,9 +60,9 @@
  *    skips the timing (the LDS rule then chooses); PVI_TUNE_VERBOSE=1 prints the choices to
  *    stderr; PVI_C_BLOCK=4|8|12|16|32 at mdp_create and the first solve keeps the plain
  *    kernels at that width wherever it fits (for tests).
- *  - Scenario A (FIFO) packs floor(64 / R) tiles into a wavefront, or 2 when that
- *    would leave fewer wavefronts than the device has SIMDs; results do not depend
- *    on the choice.  PVI_A_GROUP=<G>, 1 <= G <= floor(64 / R), read by mdp_create,
+ *  - Scenario A (FIFO) gives a wavefront one tile and splits the actions of its states
+ *    over its lanes, or packs floor(64 / R) tiles into it where that is faster (up to 11
+ *    orders and many states); results do not depend on the choice.  PVI_A_GROUP=<G>, 1 <= G <= floor(64 / R), read by mdp_create,
  *    fixes it (for tests).
  *  - Scenario B as the paper runs it (lead time 1) sums on the FP64 matrix cores for up
  *    to 32 orders of each product; PVI_B1_LANES=0 keeps the general kernels (for tests:

@@ -127,10 +127,39 @@ struct SpanIn {
     Ctl ctl;
     unsigned long long k[4];
 };
+// Field by field: a struct copy would go through private memory, and wait for it.
+__device__ __forceinline__ void ctl_copy(Ctl& to, const Ctl& from) {
+    to.mu = from.mu;
+    to.c = from.c;
+    to.dmax = from.dmax;
+    to.dmin = from.dmin;
+    to.span = from.span;
+    to.best_span = from.best_span;
+    to.thr = from.thr;
+    to.floor32 = from.floor32;
+    to.vabs = from.vabs;
+    to.stop = from.stop;
+    to.sweeps = from.sweeps;
+    to.stop_sweep = from.stop_sweep;
+    to.stall = from.stall;
+    to.fp32_phase = from.fp32_phase;
+    to.rule = from.rule;
+    to.pending = from.pending;
+}
+// Without a SpanBuf the control block of the solve alone is read (and the keys, unused, from
+// it): no branch parts the loads from those that follow.
 template <bool FP32>
-__device__ __forceinline__ void span_fetch(const SpanBuf* b, int sweep, SpanIn& in) {
-    in.ctl = b->ctl[sweep & 1];
-    const unsigned long long* k = b->key[(sweep + 3) & 3][threadIdx.x & (kSpanSlots - 1)];
+__device__ __forceinline__ void span_fetch(const SpanBuf* b, const Ctl* ctl, int sweep,
+                                           SpanIn& in) {
+    // by vector loads (the offset 0 is one the compiler cannot see): scalar loads return out
+    // of order, so the next wait for a kernel argument would wait for these
+    uint32_t zero;
+    asm("v_mov_b32 %0, 0" : "=v"(zero));
+    const Ctl* c = b ? &b->ctl[sweep & 1] : ctl;
+    ctl_copy(in.ctl, *reinterpret_cast<const Ctl*>(reinterpret_cast<const char*>(c) + zero));
+    const unsigned long long* k =
+        b ? b->key[(sweep + 3) & 3][threadIdx.x & (kSpanSlots - 1)]
+          : reinterpret_cast<const unsigned long long*>(ctl);
     in.k[0] = k[0];
     in.k[1] = k[1];
     if (FP32) {
@@ -150,19 +179,24 @@ __device__ __forceinline__ void span_reduce(SpanIn& in, int fixed, double gamma)
     span_update(in.ctl, v[0], -v[1], v[2], -v[3], FP32, fixed, gamma);
 }
 
-// The same at a sweep's start, every wavefront for itself; the first workgroup stores it for the next sweep and clears that sweep's keys.  Returns
-// whether the rule has fired; this sweep then does no work.
+// The same at a sweep's start, every wavefront for itself; the first workgroup stores it for
+// the next sweep and clears that sweep's keys.  Returns whether the rule has fired; this
+// sweep then does no work.  Without a SpanBuf the launches between the sweeps have done so.
 template <bool FP32>
 __device__ __forceinline__ bool span_apply(SpanBuf* b, int sweep, SpanIn& in, int fixed,
                                            double gamma) {
+    in.ctl.stop = __builtin_amdgcn_readfirstlane(in.ctl.stop);
+    if (!b) return in.ctl.stop;
+    in.ctl.pending = __builtin_amdgcn_readfirstlane(in.ctl.pending);
+    in.ctl.rule = __builtin_amdgcn_readfirstlane(in.ctl.rule);
     span_reduce<FP32>(in, fixed, gamma);
     in.ctl.pending = !in.ctl.stop;
     if (blockIdx.x == 0 && threadIdx.x < kSpanSlots) {
-        if (threadIdx.x == 0) b->ctl[(sweep + 1) & 1] = in.ctl;
+        if (threadIdx.x == 0) ctl_copy(b->ctl[(sweep + 1) & 1], in.ctl);
         unsigned long long* k = b->key[(sweep + 1) & 3][threadIdx.x];
         k[0] = k[1] = k[2] = k[3] = 0;
     }
-    return in.ctl.stop;
+    return __builtin_amdgcn_readfirstlane(in.ctl.stop);
 }
 
 // One wavefront's (or workgroup's) increments into the keys of its sweep, by one lane.

@@ -27,6 +27,12 @@ ADev make_adev(const pvi_mdp* p) {
     a.xt = p->xt;
     a.tab = p->tab;
     a.nz = p->m >= 2 ? (int)ipow(R, p->m - 2) : 1;
+    a.inv_nz = 1.0 / a.nz;
+    a.inv_r = 1.0 / R;
+    auto up16 = [](int q) { return q > 0 ? (65536 + q - 1) / q : 0; };
+    a.r16 = up16(R);
+    a.pair16 = up16(p->a_G * p->a_CH);
+    a.ch16 = up16(p->a_CH);
     a.r2 = p->m >= 2 ? R : 1;
     a.tiles = (int)(ipow(R, p->L - 1) * a.nz);
     // LIFO (m >= 2) has its own kernel over tiles (O, X_{m-1}..X_2); with one life
@@ -37,6 +43,11 @@ ADev make_adev(const pvi_mdp* p) {
     a.CH = p->a_CH;
     a.groups = p->dev.agroups;
     a.ngroups = p->a_G > 0 ? (int)(p->a_groups.size() / p->a_G) : 0;
+    // All of a tile's states wait in LDS while two wavefronts per SIMD or fewer run (one
+    // finishing pass: 7.7 against 8.4 us per sweep at 441 states, 21 orders); with more
+    // wavefronts to run, half of them, so that more are resident (53 against 60 us at
+    // 4,084,101 states).  Up to 11 orders all fit either way.
+    a.rows = a.ngroups <= 2048 || R <= 11 ? a.r2 : (a.r2 + 1) / 2;
     a.stride_a = ipow(R, p->m + p->L - 2);
     a.stride_h = ipow(R, p->m - 1);
     for (int i = 0; i < 8; ++i) a.pow_y[i] = (int)ipow(R, i);
@@ -435,12 +446,14 @@ pvi_status tune_c(pvi_mdp* p) {
 }  // namespace
 
 // Tiles per wavefront (G) and path points per staged chunk (CH) of the scenario-A
-// FIFO backup, chosen by timing at the first solve of a shape (R, m, L) in a process
-// and kept for every later handle of that shape.  Candidates: G = floor(64 / R), 2
-// and 1, each with the longest chunk its staging lanes allow and half of it; each is
-// timed over three FP64 sweeps (after one untimed) on this handle's buffers, with
-// the stopping rule off.  PVI_TUNE=0 keeps the rule of build_a_work_list;
-// PVI_A_GROUP and PVI_A_CHUNK fix the choice.  Results do not depend on it.
+// FIFO backup.  Up to 1,024 tiles (one wavefront per SIMD) one tile per wavefront is the
+// faster form at every shape measured (5.6 against 7.5 us per sweep at 121 states, 29.8
+// against 49.5 us at 923,521) and no timing is done.  Beyond, chosen by timing at the first
+// solve of a shape (R, m, L) in a process and kept for every later handle of that shape:
+// G = 1 and floor(64 / R), each with the longest chunk its staging lanes allow and half of
+// it, over three FP64 sweeps (after one untimed) on this handle's buffers, with the stopping
+// rule off.  PVI_TUNE=0 keeps the rule of build_a_work_list; PVI_A_GROUP and PVI_A_CHUNK fix
+// the choice.  Results do not depend on it.
 namespace {
 std::mutex g_tune_a_mu;
 std::map<TuneKey, std::pair<int, int>> g_tune_a;
@@ -448,7 +461,8 @@ std::map<TuneKey, std::pair<int, int>> g_tune_a;
 pvi_status tune_a(pvi_mdp* p) {
     const char* env = std::getenv("PVI_TUNE");
     if ((env && std::strcmp(env, "0") == 0) || std::getenv("PVI_A_GROUP") ||
-        std::getenv("PVI_A_CHUNK") || (p->d.issuing == PVI_LIFO && p->m >= 2))
+        std::getenv("PVI_A_CHUNK") || (p->d.issuing == PVI_LIFO && p->m >= 2) ||
+        make_adev(p).tiles <= 1024)
         return PVI_OK;
     const TuneKey key{p->rad[0], p->m, p->L};
     std::lock_guard<std::mutex> lock(g_tune_a_mu);
@@ -457,7 +471,7 @@ pvi_status tune_a(pvi_mdp* p) {
         auto& d = p->dev;
         std::vector<std::pair<int, int>> cand;
         const int gmax = a_group_max(p);
-        for (int G : {gmax, std::min(gmax, 2), 1})
+        for (int G : {gmax, 1})
             for (int CH : {a_chunk_max(p, G), std::max(1, a_chunk_max(p, G) / 2)})
                 if (std::find(cand.begin(), cand.end(), std::make_pair(G, CH)) == cand.end())
                     cand.emplace_back(G, CH);

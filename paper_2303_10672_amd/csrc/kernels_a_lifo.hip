@@ -28,15 +28,9 @@ template <typename VT, bool EXTRACT>
 __global__ __launch_bounds__(1024) void backup_a_lifo_kernel(ADev p) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[64];
-    Ctl* ctl = p.ctl;
     constexpr bool FP32 = sizeof(VT) == 4;
     SpanIn si;
-    if constexpr (!EXTRACT) {
-        if (p.span)
-            span_fetch<FP32>(p.span, p.sweep, si);
-        else if (ctl->stop)
-            return;
-    }
+    if constexpr (!EXTRACT) span_fetch<FP32>(p.span, p.ctl, p.sweep, si);
     const int R = p.R, m = p.m, tid = threadIdx.x, nt = blockDim.x;
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
     const int h = tile / p.nz, z = tile - h * p.nz;  // z = (X_{m-1}..X_2), X_2 fastest
@@ -83,8 +77,8 @@ __global__ __launch_bounds__(1024) void backup_a_lifo_kernel(ADev p) {
     double mu = 0.0;
     if constexpr (!EXTRACT) {
         // every wavefront comes to the same decision
-        if (p.span && span_apply<FP32>(p.span, p.sweep, si, p.fixed, p.gamma)) return;
-        if (FP32) mu = p.span ? si.ctl.mu : ctl->mu;
+        if (span_apply<FP32>(p.span, p.sweep, si, p.fixed, p.gamma)) return;
+        if (FP32) mu = si.ctl.mu;
     }
     __syncthreads();
     for (int k = tid; k < R * R; k += nt) {

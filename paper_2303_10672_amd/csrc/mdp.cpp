@@ -37,12 +37,14 @@ static int64_t ipow_i(int64_t b, int e) {
 // Work list of the scenario-A backup kernel for G tiles per wavefront (0: the rule
 // below) and CH path points per staged chunk (0: as many as the staging lanes allow).
 // One wavefront takes G tiles of equal digit sum b (so their loops run in lockstep),
-// R lanes each.  Tiles are grouped per block of G in-transit vectors and, inside one
+// R lanes each; a wavefront of one tile (G = 1) splits each state's actions over several
+// lanes instead.  Tiles are grouped per block of G in-transit vectors and, inside one
 // digit sum, by (X_m..X_3) then in-transit vector, so a full group is one (X_m..X_3)
-// over G in-transit vectors.  The rule: G = floor(64 / R), or 2 when full groups
-// would give fewer wavefronts than the chip has SIMDs (1,024): more wavefronts, and
-// each stages longer chunks of its path.  The autotuner (families.cpp) times other
-// choices at the first solve of a shape.  Results do not depend on G or CH (each
+// over G in-transit vectors.  The rule: G = 1, but floor(64 / R) for up to 11 orders where
+// that still gives two wavefronts per SIMD (2,048; 26 against 49 us per sweep at 8^7 states,
+// 29.7 against 31.3 at 11^6, while 8.5 against 13.2 us the other way at 11^5 and 53 against
+// 58 us at 21^5).  The autotuner (families.cpp) times both for the larger instances
+// at the first solve of a shape.  Results do not depend on G or CH (each
 // lane's arithmetic is its own tile's).  PVI_A_GROUP=<G> (1 .. floor(64 / R)) and
 // PVI_A_CHUNK=<CH> fix them, for tests.
 void build_a_work_list(pvi_mdp* p, int G_req, int CH_req) {
@@ -52,7 +54,7 @@ void build_a_work_list(pvi_mdp* p, int G_req, int CH_req) {
     const int64_t nzt = p->m >= 2 ? (int64_t)ipow_i(R, p->m - 2) : 1;
     const int gmax = a_group_max(p);
     p->a_G = G_req > 0 ? std::min(G_req, gmax)
-                       : (nh * nzt / gmax < 1024 ? std::min(gmax, 2) : gmax);
+                       : (R <= 11 && nh * nzt / gmax >= 2048 ? gmax : 1);
     if (const char* force = std::getenv("PVI_A_GROUP")) {
         const int g = std::atoi(force);
         if (g >= 1 && g <= gmax) p->a_G = g;
@@ -64,28 +66,28 @@ void build_a_work_list(pvi_mdp* p, int G_req, int CH_req) {
         const int c = std::atoi(force);
         if (c >= 1 && c <= chmax) p->a_CH = c;
     }
-    std::vector<int> zsum(nzt, 0);
+    // the tiles (X_m..X_3) of one in-transit vector by digit sum, each in rising order
+    const int bmax = std::max(0, p->m - 2) * (R - 1);
+    std::vector<std::vector<int32_t>> by_sum(bmax + 1);
     for (int64_t z = 0; z < nzt; ++z) {
+        int sum = 0;
         int64_t t = z;
         for (int i = 2; i <= p->m - 1; ++i) {
-            zsum[z] += (int)(t % R);
+            sum += (int)(t % R);
             t /= R;
         }
+        by_sum[sum].push_back((int32_t)z);
     }
-    const int bmax = std::max(0, p->m - 2) * (R - 1);
-    p->a_groups.clear();
+    std::vector<int32_t> list;
+    std::vector<int> gsum;  // digit sum of each group
+    list.reserve((size_t)(nh * nzt) + (size_t)(bmax + 1) * G * ((nh + G - 1) / G));
     for (int64_t hb = 0; hb < nh; hb += G) {
         const int64_t he = std::min<int64_t>(hb + G, nh);
         for (int b = bmax; b >= 0; --b) {
-            int fill = 0;
-            for (int64_t z = 0; z < nzt; ++z) {
-                if (zsum[z] != b) continue;
-                for (int64_t h = hb; h < he; ++h) {
-                    p->a_groups.push_back((int32_t)(h * nzt + z));
-                    if (++fill == G) fill = 0;
-                }
-            }
-            for (; fill != 0 && fill < G; ++fill) p->a_groups.push_back(-1);
+            for (int32_t z : by_sum[b])
+                for (int64_t h = hb; h < he; ++h) list.push_back((int32_t)(h * nzt + z));
+            while (list.size() % G) list.push_back(-1);
+            gsum.resize(list.size() / G, b);
         }
     }
     // Workgroups are dispatched round-robin over the 8 XCDs and the kernel gives
@@ -93,21 +95,23 @@ void build_a_work_list(pvi_mdp* p, int G_req, int CH_req) {
     // in-transit vectors).  Sorting each range by digit sum, longest path first,
     // makes the in-order dispatch onto freed slots a longest-first list schedule,
     // which shortens the tail of the launch.
-    const int ng = (int)(p->a_groups.size() / G), q = ng >> 3, r = ng & 7;
-    std::vector<int32_t> sorted;
-    sorted.reserve(p->a_groups.size());
+    const int ng = (int)gsum.size(), q = ng >> 3, r = ng & 7;
+    p->a_groups.resize(list.size());
+    std::vector<int> at(bmax + 1);
     for (int x = 0; x < 8; ++x) {
         const int lo = x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q;
-        const int cnt = q + (x < r ? 1 : 0);
-        std::vector<int> idx(cnt);
-        for (int k = 0; k < cnt; ++k) idx[k] = lo + k;
-        auto bsum = [&](int grp) { return zsum[p->a_groups[(size_t)grp * G] % nzt]; };
-        std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return bsum(a) > bsum(b); });
-        for (int k : idx)
-            sorted.insert(sorted.end(), p->a_groups.begin() + (size_t)k * G,
-                          p->a_groups.begin() + (size_t)(k + 1) * G);
+        const int hi = lo + q + (x < r ? 1 : 0);
+        std::fill(at.begin(), at.end(), 0);
+        for (int k = lo; k < hi; ++k) ++at[gsum[k]];
+        for (int b = bmax, n = lo; b >= 0; --b) {
+            const int c = at[b];
+            at[b] = n;
+            n += c;
+        }
+        for (int k = lo; k < hi; ++k)
+            std::copy_n(list.begin() + (size_t)k * G, G,
+                        p->a_groups.begin() + (size_t)at[gsum[k]]++ * G);
     }
-    p->a_groups.swap(sorted);
 }
 
 int a_group_max(const pvi_mdp* p) { return std::min(16, std::max(1, 64 / p->rad[0])); }

@@ -86,11 +86,14 @@ struct ADev {
     int32_t tiles;      // nh * nz
     const int32_t* groups;  // [ngroups][G] tile ids, equal digit sum per group, -1 = none
     int32_t G, CH, ngroups; // tiles per wavefront, path points per staged chunk
+    int32_t rows;       // X_2 values whose best values LDS holds at a time
     int32_t pow_y[8];   // R^(i-1), weight of next-state digit i inside a block
     int32_t fixed;      // 1: fixed number of sweeps, the stopping rule is not applied
     int32_t lifo;       // 1: LIFO issuing (tiles are (O, X_{m-1}..X_2) then)
     int32_t lmax;       // LIFO: longest backwards depletion list, (m-2)(R-1) + R
     double gamma, cvar;
+    double inv_nz, inv_r;   // 1 / nz and 1 / R: quotients of tile numbers by a multiplication
+    int32_t r16, pair16, ch16;  // ceil(2^16 / q) for q = R, G CH and CH: quotients of lanes
 };
 
 // ------------------------------------------------------------------ family B

@@ -214,3 +214,35 @@ def test_max_sweeps_not_converged_keeps_results():
     assert e.value.status == pvi.PVI_E_NOT_CONVERGED
     V = pvi.value_get(m)
     assert np.all(np.isfinite(V))
+
+
+# each compiled action count and the counts on both sides of it; the last has more than 2,048
+# wavefronts of one tile, whose states are finished in two parts
+SPLITS = [W.scenario_a(m=m, L=L, a_max=R - 1, d_max=20, demand={
+              "kind": "gamma", "mean": [0.4 * R + 1.0], "cv": [0.8]})
+          for R in (1, 2, 8, 9, 11, 12, 16, 17, 21, 24, 25, 32)
+          for m, L in ((1, 1), (2, 2), (3, 1))] + [W.scenario_a(m=4, L=2, a_max=12, d_max=25)]
+
+
+@pytest.mark.parametrize("sc", SPLITS, ids=[f"m{s['m']}L{s['L']}R{s['a_max'][0] + 1}"
+                                            for s in SPLITS])
+def test_actions_split_over_lanes_equal_whole_tiles(sc, monkeypatch):
+    """One tile per wavefront (actions split over lanes) against the oracle and, bit for bit,
+    against several tiles per wavefront; short chunks of the path give the same bits too."""
+    o = Oracle(sc)
+    R = sc["a_max"][0] + 1
+    V = W.random_values(o.n_states, seed=7)
+    ref = o.sweep(V)[0]
+    runs = []
+    for G, CH in ((1, 64), (1, 3), (2, 5), (min(16, 64 // R), 1)):
+        monkeypatch.setenv("PVI_A_GROUP", str(G))
+        monkeypatch.setenv("PVI_A_CHUNK", str(CH))
+        m = pvi.mdp_create(sc)
+        runs.append([x for prec in ("fp64", "fp32", "fp32_wide")
+                     for x in pvi.vi_backup(m, V, prec)])
+    assert relerr(runs[0][0], ref) < 1e-12
+    for prec in (3, 6):
+        assert relerr(runs[0][prec], ref) < 1e-6
+    for other in runs[1:]:
+        for x, y in zip(runs[0], other):
+            assert np.array_equal(x, y)
