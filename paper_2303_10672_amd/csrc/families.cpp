@@ -451,7 +451,7 @@ pvi_status tune_c(pvi_mdp* p) {
 // against 49.5 us at 923,521) and no timing is done.  Beyond, chosen by timing at the first
 // solve of a shape (R, m, L) in a process and kept for every later handle of that shape:
 // G = 1 and floor(64 / R), each with the longest chunk its staging lanes allow and half of
-// it, over three FP64 sweeps (after one untimed) on this handle's buffers, with the stopping
+// it, over eight FP64 sweeps (after one untimed) on this handle's buffers, with the stopping
 // rule off.  PVI_TUNE=0 keeps the rule of build_a_work_list; PVI_A_GROUP and PVI_A_CHUNK fix
 // the choice.  Results do not depend on it.
 namespace {
@@ -509,7 +509,7 @@ pvi_status tune_a(pvi_mdp* p) {
             if ((e = launch_backup_a(a, 0, 0, 0, s)) != hipSuccess ||
                 (e = hipEventRecord(e0, s)) != hipSuccess)
                 break;
-            for (int r = 0; r < 3 && e == hipSuccess; ++r) e = launch_backup_a(a, 0, 0, 0, s);
+            for (int r = 0; r < 8 && e == hipSuccess; ++r) e = launch_backup_a(a, 0, 0, 0, s);
             if (e != hipSuccess || (e = hipEventRecord(e1, s)) != hipSuccess ||
                 (e = hipEventSynchronize(e1)) != hipSuccess)
                 break;
@@ -531,7 +531,7 @@ pvi_status tune_a(pvi_mdp* p) {
         const char* verbose = std::getenv("PVI_TUNE_VERBOSE");
         if (verbose && std::strcmp(verbose, "1") == 0)
             std::fprintf(stderr, "pvi: scenario A R=%d m=%d L=%d: G=%d CH=%d (%.1f us per sweep)\n",
-                         p->rad[0], p->m, p->L, choice.first, choice.second, 1e3f * best / 3.f);
+                         p->rad[0], p->m, p->L, choice.first, choice.second, 1e3f * best / 8.f);
     }
     if (p->a_G != it->second.first || p->a_CH != it->second.second)
         build_a_work_list(p, it->second.first, it->second.second);

@@ -139,3 +139,20 @@ def test_lifo_and_supnorm_through_the_server():
     rb = pvi.mdp_create(W.config0())
     pvi.vi_solve(rb, precision="fp64", eps=1e-4, stop_rule="supnorm")
     assert np.array_equal(pvi.value_get(b), pvi.value_get(rb))
+
+
+@pytest.mark.parametrize("sc", [
+    W.scenario_a(m=6, L=1, a_max=7, d_max=30, issuing="lifo"),   # list: 288 items, 64 threads
+    W.scenario_a(m=8, L=1, a_max=2, d_max=16, issuing="lifo"),   # the longest life
+    W.scenario_a(m=3, L=1, a_max=31, d_max=40, issuing="lifo"),  # 1024 threads, 63 points
+])
+def test_lifo_lists_longer_than_a_request(sc):
+    o = Oracle(sc)
+    m = pvi.mdp_create(sc)
+    V = W.random_values(o.n_states, seed=5)
+    Vo, pio, gapo = o.sweep(V)
+    Vg, pig, gapg = pvi.vi_backup(m, V, "fp64")
+    assert np.abs(Vg - Vo).max() < 1e-12 * np.abs(Vo).max()
+    clear = gapo > 1e-9
+    assert np.array_equal(pig[clear], pio[clear])
+    assert np.allclose(gapg[clear], gapo[clear], rtol=1e-8, atol=1e-8)
