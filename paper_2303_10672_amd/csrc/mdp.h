@@ -10,6 +10,10 @@
 
 #include "pvi_internal.h"
 
+namespace pvi {
+struct HostStage;
+}
+
 struct pvi_mdp {
     pvi_mdp_desc d{};    // copy of the descriptor (table pointers cleared)
     int family = 0, m = 0, L = 0, P = 1;
@@ -73,6 +77,7 @@ struct pvi_mdp {
         pvi::SpanBuf* span = nullptr;
         pvi::Ctl* ctl = nullptr;  // span->ctl[0]
         pvi::Ctl* h_ctl = nullptr;  // pinned host mirror
+        pvi::HostStage* stage = nullptr;  // pinned chunks of large copies to the host
         double *pmf = nullptr, *cdf = nullptr, *tail = nullptr, *r0 = nullptr;
         int32_t* agroups = nullptr;
         double *z = nullptr, *rexp0 = nullptr, *epmf = nullptr, *ecdf = nullptr,
@@ -113,6 +118,9 @@ struct pvi_mdp {
 namespace pvi {
 pvi_status ensure_device(pvi_mdp* p);
 void free_device(pvi_mdp* p);
+// Blocking copy of device memory that is ready to the caller's memory (host_copy.cpp).
+hipError_t copy_to_host(pvi_mdp* p, void* dst, const void* src, size_t bytes);
+void free_host_stage(HostStage* s);
 pvi_status park_results(pvi_mdp* p);
 // vi_solve with a switch for the captured sweep graphs (off: every sweep launched
 // directly) and an optional progress counter (sweeps completed, stored at every

@@ -51,6 +51,8 @@ void free_device(pvi_mdp* p) {
         if (e) (void)hipEventDestroy(e);
     for (auto& g : d.graphs)
         if (g.exec) (void)hipGraphExecDestroy(g.exec);
+    free_host_stage(d.stage);
+    d.stage = nullptr;
     if (d.own) (void)hipStreamDestroy(d.own);
     (void)hipSetDevice(prev);
     d = pvi_mdp::Dev{};
@@ -640,8 +642,8 @@ pvi_status policy_get(const pvi_mdp* cp, int32_t* policy, double* q_gap) {
         return PVI_OK;
     }
     PVI_HIP(hipSetDevice(p->dev.device));
-    PVI_HIP(hipMemcpy(policy, p->dev.pi, sizeof(int32_t) * p->ns, hipMemcpyDeviceToHost));
-    if (q_gap) PVI_HIP(hipMemcpy(q_gap, p->dev.gap, sizeof(double) * p->ns, hipMemcpyDeviceToHost));
+    PVI_HIP(copy_to_host(p, policy, p->dev.pi, sizeof(int32_t) * p->ns));
+    if (q_gap) PVI_HIP(copy_to_host(p, q_gap, p->dev.gap, sizeof(double) * p->ns));
     return PVI_OK;
 }
 
@@ -655,7 +657,7 @@ pvi_status value_get(const pvi_mdp* cp, double* v) {
         return PVI_OK;
     }
     PVI_HIP(hipSetDevice(p->dev.device));
-    PVI_HIP(hipMemcpy(v, v64_slot(p, p->ret_buf), sizeof(double) * p->ns, hipMemcpyDeviceToHost));
+    PVI_HIP(copy_to_host(p, v, v64_slot(p, p->ret_buf), sizeof(double) * p->ns));
     return PVI_OK;
 }
 
