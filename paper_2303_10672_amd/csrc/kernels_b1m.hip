@@ -44,6 +44,25 @@ __device__ __forceinline__ d4 mfma(double a, double b, d4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+__device__ __forceinline__ double lds_f64(uint32_t a) {
+    return *(const __attribute__((address_space(3))) double*)(size_t)a;
+}
+
+__device__ __forceinline__ uint32_t lds_u16(uint32_t a) {
+    return *(const __attribute__((address_space(3))) uint16_t*)(size_t)a;
+}
+template <typename T>
+__device__ __forceinline__ uint32_t lds_address(const T* p) {
+    return (uint32_t)(size_t)(const __attribute__((address_space(3))) T*)p;
+}
+
+// max without the extra instruction that quiets signalling NaNs (no arithmetic result is one)
+__device__ __forceinline__ double max_f64(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 }  // namespace
 
 // W(A, x_b, g) for one g and one tile of 16 joint orders: the slab V(A^a, g, A^b, .) in
@@ -175,7 +194,12 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_stage_y_kernel(B1Dev p) {
 // What bounds it: the Y rows are shared by the XB vectors of a workgroup and the W tile by
 // its path groups, so registers (the running maxima, 2 KB per path group and vector) set
 // how much of L2's traffic is saved: 17 GB of Y and 8.6 GB of W per sweep at 16 orders
-// per product and m = 3 (XB = 2, GPW = 8), beside 1.5e11 flop.
+// per product and m = 3 (XB = 2, GPW = 8), beside 1.5e11 flop.  Those take 3.3 ms at the rate
+// of a chain of these instructions alone (45 ns each), and two wavefronts per SIMD hide little
+// beside them, so everything else is kept off the vector units: the weights of a step are one
+// LDS read, only a path's last step selects, padding orders lose by their cost, both vectors'
+// rows lie side by side and the maxima are single instructions.  60 such instructions per
+// path group and tile instead of 130: 5.04 ms per sweep, 5.75 before.
 template <int XB, int MT, int GPW, bool EXTRACT>
 __global__ __launch_bounds__(64 * kWaves) void b1m_final_kernel(B1Dev p) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -191,13 +215,16 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_final_kernel(B1Dev p) {
         xb[i] = __builtin_amdgcn_readfirstlane(XB == 1 ? p.xb_order[xi] : p.xb_pair[XB * xi + i]);
     const int na1p = (p.na1 + 7) & ~7;  // a staging instruction moves eight rows
     const int tabn = p.HA + 1 + kTabPad;
-    double* ws = reinterpret_cast<double*>(smem);             // [2][XB][na1p][kRow]
+    double* ws = reinterpret_cast<double*>(smem);             // [2][na1p][XB][kRow]
     double* wp = ws + (size_t)2 * XB * na1p * kRow;           // [tabn] P(D_a = h)
     double* wg = wp + tabn;                                   // [tabn] P(D_a >= h)
     double* wr = wg + tabn;                                   // [tabn] revenue of I_a at I_b
-    us4* sp = reinterpret_cast<us4*>(wr + tabn);              // [kWaves * GPW][ncha][4]
+    // [kWaves * GPW][4 ncha][4]: rows of a path's points, four per step; two steps past the
+    // last path are read, not used
+    uint16_t* sp = reinterpret_cast<uint16_t*>(wr + tabn);
     int Ib = 0;
     for (int v = xb[0]; v > 0; v /= p.Rb) Ib += v % p.Rb;
+    Ib = __builtin_amdgcn_readfirstlane(Ib);
     for (int i = tid; i < tabn; i += blockDim.x) {
         wp[i] = p.pa1[i];  // zeros past HA, as are those of ga
         wg[i] = p.ga[i];
@@ -213,8 +240,11 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_final_kernel(B1Dev p) {
     };
     for (int i = tid; i < kWaves * GPW * p.ncha * 4; i += blockDim.x) {
         const int slot = i / (p.ncha * 4), g = group_at(slot / GPW, slot % GPW);
+        const int chunk = (i >> 2) - slot * p.ncha, lk = i & 3;
         const us4* src = reinterpret_cast<const us4*>(p.apath);
-        sp[i] = src[(size_t)max(g, 0) * p.ncha * 4 + (i - slot * p.ncha * 4)];
+        const us4 row = src[((size_t)max(g, 0) * p.ncha + chunk) * 4 + lk];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) sp[(i >> 2) * 16 + s * 4 + lk] = row[s];
     }
     int grp[GPW], Kg[GPW];
 #pragma unroll
@@ -224,16 +254,15 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_final_kernel(B1Dev p) {
     }
     const int kk = lane >> 4, col = lane & 15;
     const int nrow8 = na1p / 8;
-    // tile t into buffer b: eight rows of 16 orders per instruction, 16 bytes per lane
+    // tile t into buffer b: eight runs of 16 orders per instruction, 16 bytes per lane
     auto stage = [&](int t, int b) {
         for (int i = wave; i < XB * nrow8; i += kWaves) {
-            const int v = i / nrow8, r8 = i - v * nrow8;
-            const int g = min(r8 * 8 + (lane >> 3), p.na1 - 1);
+            const int run = i * 8 + (lane >> 3), g = min(run / XB, p.na1 - 1);
             int x = xb[0];
-            if constexpr (XB > 1) x = v ? xb[1] : xb[0];
+            if constexpr (XB > 1) x = run % XB ? xb[1] : xb[0];
             const double* src =
                 p.w + ((int64_t)x * p.na1 + g) * p.nap + t * kRow + (lane & 7) * 2;
-            double* dst = ws + ((size_t)(b * XB + v) * na1p + r8 * 8) * kRow;
+            double* dst = ws + ((size_t)b * XB * na1p + i * 8) * kRow;
             __builtin_amdgcn_global_load_lds(
                 (const __attribute__((address_space(1))) void*)src,
                 (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
@@ -260,13 +289,15 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_final_kernel(B1Dev p) {
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            yoff[mt][r] = (uint32_t)(min(16 * mt + kk + 4 * r, p.Ra - 1) * p.nap + col);
+            yoff[mt][r] = (uint32_t)(min(16 * mt + kk + 4 * r, p.Ra - 1) * p.nap + col) * 8u;
     auto load_y = [&](int gi, int t, double (&y)[MT][4]) {
-        const double* src = ybase + (int64_t)max(grp[gi], 0) * (p.Ra * p.nap) + t * kRow;
+        const char* src = reinterpret_cast<const char*>(
+            ybase + (int64_t)max(grp[gi], 0) * (p.Ra * p.nap) + t * kRow);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) y[mt][r] = src[yoff[mt][r]];
+            for (int r = 0; r < 4; ++r)
+                y[mt][r] = *reinterpret_cast<const double*>(src + yoff[mt][r]);
     };
     double w0[MT];  // weights of the first four points: the first one's is cumulative
 #pragma unroll
@@ -274,6 +305,11 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_final_kernel(B1Dev p) {
         const int x1 = 16 * mt + col;
         w0[mt] = kk == 0 ? p.fa[x1] : p.pa1[x1 + kk];
     }
+    // LDS addresses of the lane: column of a tile, weights of the first four points, weights
+    // of a path's end and revenue at K = 0
+    const uint32_t ws0 = lds_address(ws) + col * 8u, wp0 = lds_address(wp) + (col + kk) * 8u;
+    const uint32_t wg0 = lds_address(wg) + col * 8u, wr0 = lds_address(wr) + kk * 8u;
+    const uint32_t sp0 = lds_address(sp) + (uint32_t)(wave * GPW * p.ncha) * 32u + kk * 2u;
     stage(0, 0);
     for (int t = 0; t < p.ntile; ++t) {
         // the staged tile has landed, and every wavefront is done with the other buffer
@@ -282,10 +318,11 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_final_kernel(B1Dev p) {
         double y[2][MT][4];
         load_y(0, t, y[0]);
         if (t + 1 < p.ntile) stage(t + 1, (t + 1) & 1);
-        const double* wt = ws + (size_t)(t & 1) * XB * na1p * kRow + col;
+        const uint32_t wt = ws0 + (uint32_t)((t & 1) * XB * na1p) * (kRow * 8u);
         const int A = t * kRow + col, aa = A / p.Rb, ab = A - aa * p.Rb;
+        // padding orders never win: their cost is the lowest value
         const bool real = A < p.Ra * p.Rb;
-        const double cost = fma(-p.cvb, (double)ab, -p.cva * aa);
+        const double cost = real ? fma(-p.cvb, (double)ab, -p.cva * aa) : -DBL_MAX;
 #pragma unroll
         for (int gi = 0; gi < GPW; ++gi) {
             if (gi + 1 < GPW) load_y(gi + 1, t, y[(gi + 1) & 1]);
@@ -294,55 +331,77 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_final_kernel(B1Dev p) {
             // tile loop for every group at once
             int K = Kg[gi];
             asm volatile("" : "+s"(K));
-            const us4* path = sp + (size_t)(wave * GPW + gi) * p.ncha * 4 + kk;
+            const int last = K >> 2;  // step of four points that holds the path's end
+            // the operands of a step are on their way while the one before is multiplied, and
+            // its rows' places in the tile one step earlier
+            struct Step {
+                double w[MT], v[XB];
+            };
+            uint32_t pa = sp0 + (uint32_t)(gi * p.ncha) * 32u, wa = wp0;
+            auto load = [&](Step& o, uint32_t row, uint32_t w) {
+                const uint32_t from = wt + row * (XB * kRow * 8u);
+#pragma unroll
+                for (int i = 0; i < XB; ++i) o.v[i] = lds_f64(from + i * (kRow * 8u));
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) o.w[mt] = lds_f64(w + 16 * mt * 8u);
+            };
             d4 acc[XB][MT];
+            auto multiply = [&](const Step& o) {
+#pragma unroll
+                for (int i = 0; i < XB; ++i)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) acc[i][mt] = mfma(o.w[mt], o.v[i], acc[i][mt]);
+            };
+            Step a, c;
+            load(a, lds_u16(pa), wa);
+            uint32_t row = lds_u16(pa + 8);
+            double wl[MT];  // weights of the path's last point
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                a.w[mt] = w0[mt];
+                wl[mt] = lds_f64(wg0 + (uint32_t)(K + 16 * mt) * 8u);
+                if (K == 0) wl[mt] = 1.0;
+            }
 #pragma unroll
             for (int i = 0; i < XB; ++i)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) acc[i][mt] = d4{0.0, 0.0, 0.0, 0.0};
-            for (int c = 0; 16 * c <= K; ++c) {
-                const us4 row = path[c * 4];
-                double v[XB][4];
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-#pragma unroll
-                    for (int i = 0; i < XB; ++i)
-                        v[i][s] = wt[(size_t)i * na1p * kRow + (int)row[s] * kRow];
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const int k0 = 16 * c + 4 * s;
-                    if (k0 > K) break;
-                    double w[MT];
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-                        w[mt] = k0 == 0 ? w0[mt] : wp[16 * mt + col + k0 + kk];
-                    if (k0 + 3 >= K) {  // the path's last point lies here
-                        const int k = k0 + kk;
-#pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) {
-                            const double wl = K > 0 ? wg[16 * mt + col + K] : 1.0;
-                            w[mt] = k < K ? w[mt] : k == K ? wl : 0.0;
-                        }
-#pragma unroll
-                        for (int i = 0; i < XB; ++i) v[i][s] = k <= K ? v[i][s] : 0.0;
-                    }
-#pragma unroll
-                    for (int i = 0; i < XB; ++i)
-#pragma unroll
-                        for (int mt = 0; mt < MT; ++mt)
-                            acc[i][mt] = mfma(w[mt], v[i][s], acc[i][mt]);
-                }
+            int left = K >> 2;  // steps before the one that holds the path's end
+            for (; left >= 2; left -= 2) {
+                load(c, row, wa + 32);
+                row = lds_u16(pa + 16);
+                multiply(a);
+                load(a, row, wa + 64);
+                row = lds_u16(pa + 24);
+                multiply(c);
+                wa += 64;
+                pa += 16;
             }
+            if (left) {
+                load(c, row, wa + 32);
+                multiply(a);
+                a = c;
+            }
+            // the last step: points before the end as ever, the end, and nothing past it
+            {
+                const int rem = K & 3;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    a.w[mt] = kk < rem ? a.w[mt] : kk == rem ? wl[mt] : 0.0;
+#pragma unroll
+                for (int i = 0; i < XB; ++i) a.v[i] = kk <= rem ? a.v[i] : 0.0;
+                multiply(a);
+            }
+            const uint32_t wk = wr0 + (uint32_t)K * 8u;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const double base = cost + wr[min(K + 16 * mt + kk + 4 * r, tabn - 1)];
+                    const double base = cost + lds_f64(wk + (16 * mt + 4 * r) * 8u);
 #pragma unroll
                     for (int i = 0; i < XB; ++i) {
-                        double q = fma(p.gamma, acc[i][mt][r] + y[gi & 1][mt][r], base);
-                        if (!real) q = -DBL_MAX;
-                        if constexpr (EXTRACT) {
+                        const double q = fma(p.gamma, acc[i][mt][r] + y[gi & 1][mt][r], base);
+                    if constexpr (EXTRACT) {
                             if (q > best[gi][i][mt][r]) {
                                 second[gi][i][mt][r] = best[gi][i][mt][r];
                                 best[gi][i][mt][r] = q;
@@ -351,7 +410,7 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_final_kernel(B1Dev p) {
                                 second[gi][i][mt][r] = q;
                             }
                         } else {
-                            best[gi][i][mt][r] = fmax(best[gi][i][mt][r], q);
+                            best[gi][i][mt][r] = max_f64(best[gi][i][mt][r], q);
                         }
                     }
                 }
@@ -462,7 +521,7 @@ namespace {
 size_t final_lds(const B1Dev& p, int xb, int gpw) {
     const size_t na1p = (size_t)((p.na1 + 7) & ~7);
     return sizeof(double) * (2 * xb * na1p * kRow + 3 * (size_t)(p.HA + 1 + kTabPad)) +
-           sizeof(us4) * (size_t)kWaves * gpw * p.ncha * 4;
+           sizeof(us4) * ((size_t)kWaves * gpw * p.ncha * 4 + 2);
 }
 
 template <int XB, int MT, int GPW, bool EXTRACT>
