@@ -400,8 +400,9 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_final_kernel(B1Dev p) {
                     const double base = cost + lds_f64(wk + (16 * mt + 4 * r) * 8u);
 #pragma unroll
                     for (int i = 0; i < XB; ++i) {
-                        const double q = fma(p.gamma, acc[i][mt][r] + y[gi & 1][mt][r], base);
+                        double q = fma(p.gamma, acc[i][mt][r] + y[gi & 1][mt][r], base);
                     if constexpr (EXTRACT) {
+                            if (!real) q = -DBL_MAX;  // also where values are infinite
                             if (q > best[gi][i][mt][r]) {
                                 second[gi][i][mt][r] = best[gi][i][mt][r];
                                 best[gi][i][mt][r] = q;
