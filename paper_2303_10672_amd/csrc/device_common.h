@@ -112,6 +112,21 @@ __device__ inline void span_update(Ctl& ctl, double a0, double a1, double a2, do
     }
 }
 
+// Orders a wavefront's LDS stores before its later LDS reads of other lanes' data
+// (no instruction: LDS requests of one wavefront are served in issue order).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// max without the extra instruction that quiets signalling NaNs (no arithmetic result is one)
+__device__ __forceinline__ double max_f64(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // ------------------------------------------------------------------ SpanBuf
 __device__ __forceinline__ unsigned long long span_key(double x) {
     const unsigned long long b = (unsigned long long)__double_as_longlong(x);

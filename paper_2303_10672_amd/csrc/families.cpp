@@ -557,9 +557,11 @@ pvi_status family_init(pvi_mdp* p) {
             return fail(PVI_E_NOMEM, "scenario A work list allocation failed");
     }
     if (p->family == PVI_FAMILY_SUBST2) {
+        std::vector<double> pmf0(p->pmf[0]);  // zeros up to the widest tiled kernel
+        pmf0.resize(std::max<size_t>(pmf0.size(), PVI_B_JMAX), 0.0);
         const size_t zn = (size_t)p->b_rows * ipow(p->rad[1], p->m);
         if (hipMalloc((void**)&d.z, sizeof(double) * zn) != hipSuccess ||
-            upload_vec(&d.pmf, p->pmf[0]) != hipSuccess ||
+            upload_vec(&d.pmf, pmf0) != hipSuccess ||
             upload_vec(&d.rexp0, p->b_rexp0) != hipSuccess ||
             upload_vec(&d.epmf, p->b_epmf) != hipSuccess ||
             upload_vec(&d.ecdf, p->b_ecdf) != hipSuccess ||
@@ -656,7 +658,9 @@ void family_free(pvi_mdp* p) {
     d.agroups = nullptr;
 }
 
-bool family_fused_span(const pvi_mdp* p) { return p->family == PVI_FAMILY_LEADTIME; }
+bool family_fused_span(const pvi_mdp* p) {
+    return p->family == PVI_FAMILY_LEADTIME || (p->family == PVI_FAMILY_SUBST2 && make_bdev(p).tiled);
+}
 
 static hipError_t family_backup_launch(pvi_mdp* p, int fp32, int kahan, int extract, int fixed,
                                        const void* vin, void* vout, hipStream_t s, int sweep);
@@ -702,6 +706,9 @@ static hipError_t family_backup_launch(pvi_mdp* p, int fp32, int kahan, int extr
         b.v_in = vin;
         b.v_out = vout;
         b.extract = extract;
+        b.fixed = fixed;
+        b.span = sweep >= 0 ? p->dev.span : nullptr;
+        b.sweep = sweep;
         return launch_backup_b(b, fp32, extract, s);
     }
     if (p->family == PVI_FAMILY_RUL_WEEKDAY) {

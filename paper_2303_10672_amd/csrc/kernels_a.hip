@@ -97,14 +97,6 @@ struct Acc<float, true> {
     __device__ __forceinline__ double value() const { return (double)s - (double)c; }
 };
 
-// Orders a wavefront's LDS stores before its later LDS reads of other lanes' data
-// (no instruction: LDS requests of one wavefront are served in issue order).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Elements between the staged chunks of two tiles of a wavefront: CH rows, padded
 // so that consecutive tiles' rows start 4 banks apart (a stride of 4 dwords modulo
 // 64); the tiles' 16-byte row reads then never share a bank.

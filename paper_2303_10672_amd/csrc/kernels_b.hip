@@ -242,9 +242,14 @@ __device__ __forceinline__ int b_path_offset(const int (&v)[8], int m, int radix
 // and their order are those of subst_stage1_kernel; the terms that kernel skips
 // (total demand beyond emax) enter here with weight zero, which leaves every sum
 // unchanged.
+// The first kernel of a sweep, it also applies the sweep before (SpanBuf).  It has about a
+// wavefront per SIMD at 50,625 states, so what bounds it is the chain of waits; everything a
+// cell reads is requested before the first (11.9 -> 11.1 us per sweep there).
 template <typename VT, int KB, int M>
 __global__ __launch_bounds__(64) void subst_stage1_tiled_kernel(BDev p) {
-    if (p.ctl->stop && !p.extract) return;
+    constexpr bool FP32 = sizeof(VT) == 4;
+    SpanIn si;
+    span_fetch<FP32>(p.span, p.ctl, p.sweep, si);
     const int R1 = p.r1, m = M > 0 ? M : p.m;
     const int nbi = p.nb / R1;  // middle digits B_2..B_{m-1}
     const int nq = (nbi + 3) >> 2;
@@ -271,20 +276,36 @@ __global__ __launch_bounds__(64) void subst_stage1_tiled_kernel(BDev p) {
         }
     }
     const VT* Vr = reinterpret_cast<const VT*>(p.v_in) + (int64_t)i0n * p.nb;
-    const ConstF64B Fu = (ConstF64B)(p.e_cdf + (size_t)u * p.ew);
+    const double* Fu = p.e_cdf + (size_t)u * p.ew;
     const ConstF64B Pu = (ConstF64B)(p.ppad + (size_t)u * p.ewp);
     const double* Gu = p.gpad + (size_t)u * p.ewp;
     auto load = [&](int k) { return (double)Vr[b_path_offset<M>(v, m, R1, k)]; };
 
-    double acc[kBX];
-    {
-        const double v0 = load(0);
+    // All a cell reads is requested before the first wait: the weights F_u(x1) of the path's
+    // first point by a lane each (through LDS), its end's weights and revenues by x1.
+    __shared__ double sF[kBX];
+    const double f = Fu[min(a1l, p.emax)], v0 = load(0), vK = (double)Vr[0];
+    double pv[KB > 0 ? KB : 1], ge[kBX], rx[kBX];
+    if constexpr (KB > 0) {
+        // points 1 .. K - 1 with K < KB (any k gives an offset inside the row)
 #pragma unroll
-        for (int x1 = 0; x1 < kBX; ++x1) {
-            acc[x1] = 0.0;
-            const double w = K == 0 ? 1.0 : Fu[min(x1, p.emax)];
-            acc[x1] = fma(w, v0, acc[x1]);
-        }
+        for (int k = 1; k < KB; ++k) pv[k] = load(k);
+    }
+#pragma unroll
+    for (int x1 = 0; x1 < kBX; ++x1) {
+        ge[x1] = Gu[x1 + K];
+        rx[x1] = p.rexp1[(size_t)u * p.sw + K + min(x1, R1 - 1)];
+    }
+    if (!p.extract && span_apply<FP32>(p.span, p.sweep, si, p.fixed, p.gamma)) return;
+    if (lane < kBX) sF[lane] = f;
+    wave_sync();
+
+    double acc[kBX];
+#pragma unroll
+    for (int x1 = 0; x1 < kBX; ++x1) {
+        acc[x1] = 0.0;
+        const double w = K == 0 ? 1.0 : sF[x1];
+        acc[x1] = fma(w, v0, acc[x1]);
     }
     auto step = [&](int k, double vk) {
         if (k < K) {
@@ -293,12 +314,6 @@ __global__ __launch_bounds__(64) void subst_stage1_tiled_kernel(BDev p) {
         }
     };
     if constexpr (KB > 0) {
-        // points 1 .. K - 1 with K < KB: every value of the path is loaded before the
-        // first is used (any k gives an offset inside the row), so a wavefront waits
-        // for memory once
-        double pv[KB];
-#pragma unroll
-        for (int k = 1; k < KB; ++k) pv[k] = load(k);
 #pragma unroll
         for (int k = 1; k < KB; ++k) step(k, pv[k]);
     } else {
@@ -321,13 +336,11 @@ __global__ __launch_bounds__(64) void subst_stage1_tiled_kernel(BDev p) {
     }
     // the path's end: every younger unit gone, weight P_u(e >= x1 + K)
     if (K > 0) {
-        const double vK = (double)Vr[0];
 #pragma unroll
-        for (int x1 = 0; x1 < kBX; ++x1) acc[x1] = fma(Gu[x1 + K], vK, acc[x1]);
+        for (int x1 = 0; x1 < kBX; ++x1) acc[x1] = fma(ge[x1], vK, acc[x1]);
     }
     if (!live) return;
     double* zr = p.z + (int64_t)row * p.nb * R1 + (int64_t)bi * R1 * R1 + a1;
-    const double* rx = p.rexp1 + (size_t)u * p.sw + K;
 #pragma unroll
     for (int x1 = 0; x1 < kBX; ++x1)
         if (x1 < R1) zr[x1 * R1] = rx[x1] + p.gamma * acc[x1];
@@ -342,18 +355,32 @@ __global__ __launch_bounds__(64) void subst_stage1_tiled_kernel(BDev p) {
 // subst_stage2_kernel (d0 ascending), so the values are the same; the maximum over
 // a1 is a 16-lane transpose-reduction, over a0 one over four lane groups and the
 // four wavefronts.
-template <typename VT, int J, bool EXTRACT>
+// Bound by its chain of waits more than by its 200 multiply-adds per thread: 26 us per sweep
+// at 50,625 states before, 20 now.  The weights come by wide scalar loads (one load, wait and
+// select each before), the revenues through LDS (16 loads per thread after the sums before),
+// the sweep's maxima in two halves of x0 within a wavefront (20 KB of LDS and no barrier,
+// against 37 KB), and the old value is requested at the start.
+template <typename VT, int J, int M, bool EXTRACT>
 __global__ __launch_bounds__(256) void subst_stage2_tiled_kernel(BDev p) {
-    constexpr int TS = kBX + 2;  // row stride of the Q tile (16-byte rows, spread banks)
-    __shared__ int32_t roff[kBX * J];
+    constexpr bool FP32 = sizeof(VT) == 4;
+    constexpr int XS = EXTRACT ? kBX : kBX / 2;  // values of x0 in the Q tile at a time
+    constexpr int TS = XS + 2;  // row stride of the Q tile (16-byte rows, spread banks)
+    constexpr int JS = (J + 3) / 4 * 4;
+    __shared__ __align__(16) int32_t roff[kBX * JS];
     __shared__ __align__(16) double qt[kBX * kBX * TS];  // [a0][a1][x0]
     __shared__ double red[4 * kBX];
     __shared__ double red2[EXTRACT ? 4 * kBX : 1];
     __shared__ int32_t reda[EXTRACT ? 4 * kBX : 1];
-    if (!EXTRACT && p.ctl->stop) return;
+    // with a SpanBuf, stage 1 has left the sweep's control block in the copy that it writes
+    const Ctl* ctl = p.span ? &p.span->ctl[(p.sweep + 1) & 1] : p.ctl;
+    if (!EXTRACT && ctl->stop) return;
     const int grp = xcd_remap(blockIdx.x, gridDim.x);
     const int ib = grp / p.nw, wi = grp - ib * p.nw;
-    const int R0 = p.r0, R1 = p.r1, m = p.m, tid = threadIdx.x;
+    const int R0 = p.r0, R1 = p.r1, m = M > 0 ? M : p.m, tid = threadIdx.x;
+    const int64_t state = (int64_t)(min(tid, R0 - 1) + R0 * wi) * p.nb + ib;
+    __shared__ double rx[2 * kBX];  // rexp0 from the middle digits' stock on
+    double old = 0.0;
+    if (!EXTRACT && tid < kBX) old = (double)reinterpret_cast<const VT*>(p.v_in)[state];
     // middle product-0 digits w[1..m-2] = A_2..A_{m-1}
     int w[8];
     int held = 0;
@@ -369,23 +396,22 @@ __global__ __launch_bounds__(256) void subst_stage2_tiled_kernel(BDev p) {
             held += w[j];
         }
     }
+    // (entries past 2 (R0 - 1) serve only x0 that are no states)
+    if (tid < 2 * kBX) rx[tid] = p.rexp0[held + min(tid, 2 * (R0 - 1))];
     // element offset of the Z row at point j of tile a0 (rows of nb * R1 entries)
     const int zrow = p.nb * R1;
+    // the Z row at point j of tile t
+    auto row_at = [&](int t, int j) {
+        const int K = held + t;
+        int v[8];
+#pragma unroll
+        for (int d = 1; d < 8; ++d) v[d] = d == m - 1 ? t : w[d];
+        const int on_path = b_path_offset<M>(v, m, R0, j), past = p.na + (j - K) - 1;
+        return t >= R0 || j > p.d0max ? 0 : j > K ? past : on_path;
+    };
     for (int e = tid; e < kBX * J; e += blockDim.x) {
         const int t = e / J, j = e - t * J;
-        int row = 0;
-        if (t < R0 && j <= p.d0max) {
-            const int K = held + t;
-            if (j <= K) {
-                int v[8];
-#pragma unroll
-                for (int d = 1; d < 8; ++d) v[d] = d == m - 1 ? t : w[d];
-                row = b_path_offset(v, m, R0, j);
-            } else {
-                row = p.na + (j - K) - 1;
-            }
-        }
-        roff[e] = row * zrow;
+        roff[t * JS + j] = row_at(t, j) * zrow;
     }
     __syncthreads();
 
@@ -394,18 +420,18 @@ __global__ __launch_bounds__(256) void subst_stage2_tiled_kernel(BDev p) {
     const double* zc = p.z + (int64_t)ib * R1 + a1;
     double zr[J];
 #pragma unroll
-    for (int j = 0; j < J; ++j) zr[j] = zc[roff[a0 * J + j]];
+    for (int j = 0; j < J; ++j) zr[j] = zc[(uint32_t)roff[a0 * JS + j]];
 
     // demand values past d0max (up to J) add terms of weight zero, which leave the
-    // sums unchanged
+    // sums unchanged.  (Zeros follow the PMF in memory: the weights come by a few wide scalar
+    // loads, not by one load, wait and select each.)
     const ConstF64B P0 = (ConstF64B)p.pmf0;
-    const int d0max = p.d0max;
     double acc[kBX];
 #pragma unroll
     for (int x0 = 0; x0 < kBX; ++x0) acc[x0] = 0.0;
 #pragma unroll
     for (int d0 = 0; d0 < J; ++d0) {
-        const double pr = d0 <= d0max ? P0[min(d0, d0max)] : 0.0;
+        const double pr = P0[d0];
 #pragma unroll
         for (int x0 = 0; x0 < kBX; ++x0) acc[x0] = fma(pr, zr[d0 > x0 ? d0 - x0 : 0], acc[x0]);
     }
@@ -415,22 +441,25 @@ __global__ __launch_bounds__(256) void subst_stage2_tiled_kernel(BDev p) {
     // values go to LDS as [a0][a1][x0]; thread (a0, x0) then takes the maximum over
     // a1, and over a0 two lane exchanges and the four wavefronts follow.
     const bool real = wv * 4 + ((tid >> 4) & 3) < R0 && l16 < R1;
-    {
-        double2* row = reinterpret_cast<double2*>(qt + (size_t)(tid >> 4) * kBX * TS + l16 * TS);
+    double2* qrow = reinterpret_cast<double2*>(qt + (size_t)(tid >> 4) * kBX * TS + l16 * TS);
+    // Q values x0 = first .. first + XS - 1 to the thread's row of the tile
+    auto put = [&](int first) {
 #pragma unroll
-        for (int x0 = 0; x0 < kBX; x0 += 2) {
+        for (int i = 0; i < XS; i += 2) {
+            const int x0 = first + i;
             const double q0 = fma(-p.cvar1, (double)a1,
-                                  fma(-p.cvar0, (double)a0, p.rexp0[min(x0, R0 - 1) + held + a0])) +
+                                  fma(-p.cvar0, (double)a0, rx[x0 + a0])) +
                               acc[x0];
             const double q1 = fma(-p.cvar1, (double)a1,
                                   fma(-p.cvar0, (double)a0,
-                                      p.rexp0[min(x0 + 1, R0 - 1) + held + a0])) +
+                                      rx[x0 + 1 + a0])) +
                               acc[x0 + 1];
-            row[x0 / 2] = EXTRACT && !real ? make_double2(-DBL_MAX, -DBL_MAX) : make_double2(q0, q1);
+            qrow[i / 2] = EXTRACT && !real ? make_double2(-DBL_MAX, -DBL_MAX) : make_double2(q0, q1);
         }
-    }
-    __syncthreads();
+    };
     if constexpr (EXTRACT) {
+        put(0);
+        __syncthreads();
         // (best, second, argmax) with ties to the lowest action a0 R1 + a1, as the
         // per-state kernel takes them
         const int a0s = tid >> 4;
@@ -471,27 +500,33 @@ __global__ __launch_bounds__(256) void subst_stage2_tiled_kernel(BDev p) {
         }
         return;
     }
-    double best;
-    {
-        const double* col = qt + (size_t)(tid >> 4) * kBX * TS + l16;
-        best = col[0];
+    // lane l16 takes x0 = l16 % 8 of each half over eight values of a1, and meets lane
+    // l16 ^ 8; a wavefront reads only rows that it wrote
+    double best = -DBL_MAX;
 #pragma unroll
-        for (int i = 1; i < kBX; ++i) best = fmax(best, col[i * TS]);
+    for (int half = 0; half < 2; ++half) {
+        put(half * XS);
+        wave_sync();
+        const double* col = qt + ((size_t)(tid >> 4) * kBX + (l16 & 8)) * TS + (l16 & 7);
+        double b = col[0];
+#pragma unroll
+        for (int i = 1; i < 8; ++i) b = max_f64(b, col[i * TS]);
+        b = max_f64(b, __shfl_xor(b, 8, 64));
+        if (half == 0 || l16 >= 8) best = b;
+        wave_sync();
     }
-    best = fmax(best, __shfl_xor(best, 16, 64));
-    best = fmax(best, __shfl_xor(best, 32, 64));
+    best = max_f64(best, __shfl_xor(best, 16, 64));
+    best = max_f64(best, __shfl_xor(best, 32, 64));
     if ((tid & 63) < kBX) red[wv * kBX + l16] = best;
     __syncthreads();
     if (tid >= 64) return;
-    const double mu = sizeof(VT) == 4 ? p.ctl->mu : 0.0;
+    const double mu = FP32 ? ctl->mu : 0.0;
     double dmx = -DBL_MAX, dmn = DBL_MAX, vmx = -DBL_MAX, vmn = DBL_MAX;
     if (tid < R0) {
         const double b = fmax(fmax(red[tid], red[kBX + tid]), fmax(red[2 * kBX + tid], red[3 * kBX + tid]));
-        const int64_t s = (int64_t)(tid + R0 * wi) * p.nb + ib;
         const VT o = (VT)(b - mu);
-        reinterpret_cast<VT*>(p.v_out)[s] = o;
-        const double out = (double)o;
-        const double dv = out - (double)reinterpret_cast<const VT*>(p.v_in)[s];
+        reinterpret_cast<VT*>(p.v_out)[state] = o;
+        const double out = (double)o, dv = out - old;
         dmx = dv;
         dmn = dv;
         vmx = out;
@@ -499,15 +534,39 @@ __global__ __launch_bounds__(256) void subst_stage2_tiled_kernel(BDev p) {
     }
     dmx = wave_max(dmx);
     dmn = wave_min(dmn);
-    vmx = wave_max(vmx);
-    vmn = wave_min(vmn);
+    if (FP32 || !p.span) {
+        vmx = wave_max(vmx);
+        vmn = wave_min(vmn);
+    }
     if (tid == 0) {
+        if (p.span) {
+            span_emit<FP32>(p.span, p.sweep, grp, dmx, dmn, vmx, vmn);
+            return;
+        }
         double* pp = p.partials + 4 * (size_t)grp;
         pp[0] = dmx;
         pp[1] = dmn;
         pp[2] = vmx;
         pp[3] = vmn;
     }
+}
+
+template <typename VT, int M, bool EXTRACT>
+static hipError_t launch_b_stage2(const BDev& p, dim3 grid, hipStream_t s) {
+    const dim3 block(256);
+    // the fewest demand values J >= d0max + 1 of the compiled widths
+    if (p.d0max < 8)
+        hipLaunchKernelGGL((subst_stage2_tiled_kernel<VT, 8, M, EXTRACT>), grid, block, 0, s, p);
+    else if (p.d0max < 16)
+        hipLaunchKernelGGL((subst_stage2_tiled_kernel<VT, 16, M, EXTRACT>), grid, block, 0, s, p);
+    else if (p.d0max == 20)  // demand folded at 20, the paper's truncation
+        hipLaunchKernelGGL((subst_stage2_tiled_kernel<VT, 21, M, EXTRACT>), grid, block, 0, s, p);
+    else if (p.d0max < 24)
+        hipLaunchKernelGGL((subst_stage2_tiled_kernel<VT, 24, M, EXTRACT>), grid, block, 0, s, p);
+    else
+        hipLaunchKernelGGL((subst_stage2_tiled_kernel<VT, PVI_B_JMAX, M, EXTRACT>), grid, block, 0,
+                           s, p);
+    return hipGetLastError();
 }
 
 template <typename VT, bool EXTRACT>
@@ -530,22 +589,9 @@ static hipError_t launch_b_t(const BDev& p, hipStream_t s) {
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         const dim3 grid((unsigned)(p.nb * p.nw));
-        // the fewest demand values J >= d0max + 1 of the compiled widths
-        if (p.d0max < 8)
-            hipLaunchKernelGGL((subst_stage2_tiled_kernel<VT, 8, EXTRACT>), grid, dim3(256), 0, s, p);
-        else if (p.d0max < 16)
-            hipLaunchKernelGGL((subst_stage2_tiled_kernel<VT, 16, EXTRACT>), grid, dim3(256), 0, s,
-                               p);
-        else if (p.d0max == 20)  // demand folded at 20, the paper's truncation
-            hipLaunchKernelGGL((subst_stage2_tiled_kernel<VT, 21, EXTRACT>), grid, dim3(256), 0, s,
-                               p);
-        else if (p.d0max < 24)
-            hipLaunchKernelGGL((subst_stage2_tiled_kernel<VT, 24, EXTRACT>), grid, dim3(256), 0, s,
-                               p);
-        else
-            hipLaunchKernelGGL((subst_stage2_tiled_kernel<VT, PVI_B_JMAX, EXTRACT>), grid, dim3(256),
-                               0, s, p);
-        return hipGetLastError();
+        if (p.m == 2) return launch_b_stage2<VT, 2, EXTRACT>(p, grid, s);
+        if (p.m == 3) return launch_b_stage2<VT, 3, EXTRACT>(p, grid, s);
+        return launch_b_stage2<VT, 0, EXTRACT>(p, grid, s);
     } else {
         const int64_t n1 = (int64_t)p.rows * p.nb * p.r1;
         hipLaunchKernelGGL((subst_stage1_kernel<VT>), dim3((unsigned)((n1 + 255) / 256)), dim3(256),

@@ -56,13 +56,6 @@ __device__ __forceinline__ uint32_t lds_address(const T* p) {
     return (uint32_t)(size_t)(const __attribute__((address_space(3))) T*)p;
 }
 
-// max without the extra instruction that quiets signalling NaNs (no arithmetic result is one)
-__device__ __forceinline__ double max_f64(double a, double b) {
-    double r;
-    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
 }  // namespace
 
 // W(A, x_b, g) for one g and one tile of 16 joint orders: the slab V(A^a, g, A^b, .) in

@@ -68,15 +68,20 @@ void build_a_work_list(pvi_mdp* p, int G_req, int CH_req) {
     }
     // the tiles (X_m..X_3) of one in-transit vector by digit sum, each in rising order
     const int bmax = std::max(0, p->m - 2) * (R - 1);
-    std::vector<std::vector<int32_t>> by_sum(bmax + 1);
+    std::vector<int> zsum(nzt), from(bmax + 2, 0);
     for (int64_t z = 0; z < nzt; ++z) {
-        int sum = 0;
         int64_t t = z;
         for (int i = 2; i <= p->m - 1; ++i) {
-            sum += (int)(t % R);
+            zsum[z] += (int)(t % R);
             t /= R;
         }
-        by_sum[sum].push_back((int32_t)z);
+        ++from[zsum[z] + 1];
+    }
+    for (int b = 0; b <= bmax; ++b) from[b + 1] += from[b];
+    std::vector<int32_t> by_sum(nzt);
+    {
+        std::vector<int> next(from.begin(), from.end() - 1);
+        for (int64_t z = 0; z < nzt; ++z) by_sum[next[zsum[z]]++] = (int32_t)z;
     }
     std::vector<int32_t> list;
     std::vector<int> gsum;  // digit sum of each group
@@ -84,8 +89,8 @@ void build_a_work_list(pvi_mdp* p, int G_req, int CH_req) {
     for (int64_t hb = 0; hb < nh; hb += G) {
         const int64_t he = std::min<int64_t>(hb + G, nh);
         for (int b = bmax; b >= 0; --b) {
-            for (int32_t z : by_sum[b])
-                for (int64_t h = hb; h < he; ++h) list.push_back((int32_t)(h * nzt + z));
+            for (int k = from[b]; k < from[b + 1]; ++k)
+                for (int64_t h = hb; h < he; ++h) list.push_back((int32_t)(h * nzt + by_sum[k]));
             while (list.size() % G) list.push_back(-1);
             gsum.resize(list.size() / G, b);
         }
@@ -116,8 +121,8 @@ void build_a_work_list(pvi_mdp* p, int G_req, int CH_req) {
 
 int a_group_max(const pvi_mdp* p) { return std::min(16, std::max(1, 64 / p->rad[0])); }
 
-// The kernel pads the actions to RMAX = 8, 16, 24 or 32 and stages each path point
-// with RMAX / 8 lanes of 8 actions: CH points per chunk of G tiles fill <= 64 lanes.
+// The kernel stages each path point with one lane per 8 actions (R = 11 and 21: per 6 and
+// 7): CH points per chunk of G tiles fill <= 64 lanes.
 int a_chunk_max(const pvi_mdp* p, int G) {
     const int R = p->rad[0];
     const int rmax = R <= 8 ? 8 : R <= 16 ? 16 : R <= 24 ? 24 : 32;

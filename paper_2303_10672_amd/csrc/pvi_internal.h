@@ -106,7 +106,7 @@ struct BDev {
     double* gap;
     double* partials;   // [nb][4]
     double* z;          // [rows][nb * r1] stage-1 table
-    const double* pmf0;   // [d0max+1]
+    const double* pmf0;   // [d0max+1], then zeros up to PVI_B_JMAX entries
     const double* rexp0;  // [stock0]: c_rev0 E[min(d0, stock0)]
     const double* e_pmf;  // [d0max+1][ew]: product-1 demand incl. substitutes, given u0
     const double* e_cdf;
@@ -115,6 +115,8 @@ struct BDev {
     const double* ppad;   // [d0max+1][ewp]: e_pmf rows, zero past emax (tiled kernels)
     const double* gpad;   // [d0max+1][ewp]: e_tail rows, zero past emax
     Ctl* ctl;
+    SpanBuf* span;        // not null (tiled sweeps): no span launch follows this sweep
+    int32_t sweep, fixed;
     int32_t m, r0, r1, r1pad, na, nb, rows, d0max, emax, ew, sw, extract;
     int32_t tiled;  // sweeps use the tiled kernels (one partial per (ib, middle digits))
     int32_t nw;     // r0^(m-2): middle product-0 digit combinations

@@ -106,3 +106,31 @@ def test_tiled_kernels_match_per_cell_kernels(sc, monkeypatch):
     assert np.array_equal(ap[0], bp[0]) and np.array_equal(ap[1], bp[1])
     assert (af, ad) == (bf, bd) and np.array_equal(aW, bW)
     assert relerr(a64[0], o.sweep(V)[0]) < 1e-12
+
+
+# both sides of each compiled number of demand values, each compiled life and the general one,
+# the fewest and most orders; paths shorter and longer than a request
+WIDTHS = [W.scenario_b(m=2, a_max=(r, 16 - r), d_max=(d, 12), means=(0.4 * d + 0.5, 3.0), rho=0.6)
+          for r, d in ((1, 0), (15, 7), (8, 8), (1, 15), (15, 16), (8, 20), (3, 21), (12, 23),
+                       (4, 24), (7, 31))] + [
+    W.scenario_b(m=3, a_max=(3, 15), d_max=(9, 9), means=(3.0, 4.0), rho=0.3),
+    W.scenario_b(m=3, a_max=(2, 8), d_max=(20, 9), means=(3.0, 4.0), rho=0.3),
+    W.scenario_b(m=4, a_max=(2, 3), d_max=(6, 9), means=(2.0, 3.0), rho=0.5),
+    W.scenario_b(m=4, a_max=(1, 15), d_max=(5, 6), means=(1.0, 6.0), rho=1.0)]
+
+
+@pytest.mark.parametrize("sc", WIDTHS)
+def test_tiled_widths_match_per_cell_kernels(sc, monkeypatch):
+    runs = []
+    for tiled in ("0", "1"):
+        monkeypatch.setenv("PVI_B_TILED", tiled)
+        m = pvi.mdp_create(sc)
+        V = W.random_values(m.n_states, seed=13, scale=5.0, offset=40.0)
+        out = [*pvi.vi_backup(m, V, "fp64"), *pvi.vi_backup(m, V, "fp32")]
+        for kw in (dict(precision="fp64"), dict(precision="fp32"), dict(fixed_sweeps=9)):
+            res = pvi.vi_solve(m, **kw)
+            out += [res["sweeps_fp32"], res["sweeps_fp64"], res["dmax"], res["dmin"],
+                    pvi.value_get(m), *pvi.policy_get(m)]
+        runs.append(out)
+    for x, y in zip(*runs):
+        assert np.array_equal(x, y)

@@ -4,8 +4,11 @@ library) against vi_solve's FP64 solve, through the C ABI.
 Same kernels in the same order, so V, policy, Q gap and sweep counts are compared
 bit for bit.  Two calls in a row, the second on a smaller instance, show that the
 array's leftovers from one call never reach the next.  Sizes beyond the array's
-limits and unsupported options are refused.
+limits and unsupported options are refused.  Large results copied to the host are
+compared with it too.
 """
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -89,3 +92,36 @@ def test_refused():
     with pytest.raises(pvi.PviError) as e:
         pvi.vi_solve_noalloc(m0, 0, pi.data_ptr(), gap.data_ptr())
     assert e.value.status == pvi.PVI_E_INVALID
+
+
+@pytest.mark.parametrize("m,L,a_max", [(4, 2, 19), (4, 2, 20)])
+def test_large_results_reach_the_host_whole(m, L, a_max):
+    """3.2 M states (V and gap copied in chunks) and 4.1 M (the policy too): the values that the
+    device holds, from several threads at once, and into pinned memory."""
+    sc = W.scenario_a(m=m, L=L, a_max=a_max, d_max=12)
+    h = pvi.mdp_create(sc)
+    pvi.vi_solve(h, precision="fp64", fixed_sweeps=2)
+    n = h.n_states
+    dev = torch.empty(n, dtype=torch.int32, device="cuda")
+    pvi.policy_get_device(h, dev.data_ptr())
+    pol, gap = pvi.policy_get(h)
+    V = pvi.value_get(h)
+    assert np.array_equal(pol, dev.cpu().numpy())
+    ref = pvi.mdp_create(sc)
+    dv = torch.empty(n, dtype=torch.float64, device="cuda")
+    dg = torch.empty(n, dtype=torch.float64, device="cuda")
+    pvi.vi_solve_noalloc(ref, dv.data_ptr(), dev.data_ptr(), dg.data_ptr(), fixed_sweeps=2)
+    assert np.array_equal(V, dv.cpu().numpy()) and np.array_equal(gap, dg.cpu().numpy())
+    out = []
+    ts = [threading.Thread(target=lambda: out.append((pvi.value_get(h), *pvi.policy_get(h))))
+          for _ in range(3)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert len(out) == 3
+    for v, p, g in out:
+        assert np.array_equal(v, V) and np.array_equal(p, pol) and np.array_equal(g, gap)
+    pinned = torch.empty(n, dtype=torch.float64).pin_memory().numpy()
+    pvi._check(pvi._lib.value_get(h.handle, pvi._dptr(pinned)), "value_get")
+    assert np.array_equal(pinned, V)
