@@ -112,8 +112,13 @@ __device__ __forceinline__ void kpis(double* k, const Tally& c, int horizon) {
 
 }  // namespace
 
+// The most customers of a day that can be unmet and take the other product.
+__host__ __device__ __forceinline__ int units_max(const SimDev& s, int family) {
+    return family == 1 ? s.dmax0 : s.dmax1;
+}
+
 // The numbers of one (rollout, day), which no policy changes: the demands of both products
-// in the halves of `dem`; bit i of `bits` is whether the i-th unmet customer accepts
+// in the halves of `dem`; bit i of `bits` (32-bit words for up to 31 customers) is whether the i-th unmet customer accepts
 // substitution (two products), and scenario C's `life` has a word per remaining life k - 1,
 // bit i set when the i-th unit ordered arrives with life k (life independent of the order).
 // One thread per (rollout, day); [day][rollout], so a wavefront of rollouts reads lines.
@@ -147,7 +152,10 @@ __global__ __launch_bounds__(256) void draw_kernel(SimDev s) {
                 if ((u & 3) == 0) bu = philox(s.seed, r, (uint64_t)t, (uint64_t)(1 + (u >> 2)));
                 if (unif(word(bu, u & 3)) < s.rho) bits |= 1ull << u;
             }
-            s.bits[i] = bits;
+            if (units_max(s, FAM) <= 31)
+                reinterpret_cast<uint32_t*>(s.bits)[i] = (uint32_t)bits;
+            else
+                s.bits[i] = bits;
         }
         if (FAM == 2) {
             uint32_t life[kMaxM] = {};
@@ -175,7 +183,7 @@ __global__ __launch_bounds__(256) void draw_kernel(SimDev s) {
 // M > 0: compiled for m = M; LO >= 0: scenario A compiled for L - 1 = LO orders in transit
 // (0 for the other families; -1: up to kMaxO).  PRE: the day's numbers come from
 // draw_kernel, else they are drawn here.  SPLIT: per-product KPIs are kept.
-template <int FAM, int M, int LO, bool PRE, bool SPLIT>
+template <int FAM, int M, int LO, bool PRE, bool SPLIT, bool BITS32 = false>
 __global__ __launch_bounds__(64) void rollout_kernel(SimDev s) {
     extern __shared__ __align__(16) unsigned char smem[];
     double* cdf0 = reinterpret_cast<double*>(smem);
@@ -245,12 +253,14 @@ __global__ __launch_bounds__(64) void rollout_kernel(SimDev s) {
     // the numbers of the day after are on their way while this one is walked
     uint32_t dem = 0, dem_next = 0;
     uint64_t bits = 0, bits_next = 0;
+    uint32_t bits32 = 0, bits32_next = 0;  // BITS32: at most 31 customers
     uint32_t life[MM] = {}, life_next[MM] = {};
     const int64_t ndraw = (int64_t)s.n_roll * days;
     auto fetch = [&](int t) {
         const int64_t i = (int64_t)(t < days ? t : days - 1) * s.n_roll + rr;
         dem_next = s.dem[i];
-        if (kTwo) bits_next = s.bits[i];
+        if (kTwo && BITS32) bits32_next = reinterpret_cast<const uint32_t*>(s.bits)[i];
+        if (kTwo && !BITS32) bits_next = s.bits[i];
         if (FAM == 2) {
 #pragma unroll
             for (int j = 0; j < MM; ++j)
@@ -258,6 +268,21 @@ __global__ __launch_bounds__(64) void rollout_kernel(SimDev s) {
         }
     };
     if constexpr (PRE) fetch(0);
+    // a heuristic's parameters: read once; scenario C's pair of the day after with its numbers
+    const bool heuristic = s.kind != PVI_POLICY_TABLE;
+    int par[2] = {}, par_next[2] = {};
+    auto fetch_pair = [&](int wd) {
+        if (heuristic) {
+            par_next[0] = prm[2 * wd];
+            par_next[1] = prm[2 * wd + 1];
+        }
+    };
+    if (FAM == 2) {
+        fetch_pair(tau);
+    } else if (heuristic) {
+        par[0] = prm[0];
+        par[1] = prm[1];
+    }
     auto sum_of = [&](const int (&S)[MM + 1]) {
         int n = 0;
 #pragma unroll
@@ -291,14 +316,20 @@ __global__ __launch_bounds__(64) void rollout_kernel(SimDev s) {
         if constexpr (PRE) {
             dem = dem_next;
             bits = bits_next;
+            bits32 = bits32_next;
 #pragma unroll
             for (int j = 0; j < MM; ++j) life[j] = life_next[j];
             fetch(t + 1);
         }
+        if (FAM == 2) {
+            par[0] = par_next[0];
+            par[1] = par_next[1];
+            fetch_pair(tau + 1 == s.P ? 0 : tau + 1);
+        }
         // ---- action (two products: aA, aB; heuristic orders are not capped,
         // except scenario C's, whose remaining-life table ends at a_max)
         int a = 0, aA = 0, aB = 0;
-        if (s.kind == PVI_POLICY_TABLE) {
+        if (!heuristic) {
             // a table has fewer than 2^31 entries: the index fits 32 bits
             uint32_t idx = FAM == 2 ? (uint32_t)tau * (uint32_t)s.pw0[m - 1] : 0;
             if (FAM == 0) {
@@ -321,16 +352,15 @@ __global__ __launch_bounds__(64) void rollout_kernel(SimDev s) {
             int I = sum_of(X);
 #pragma unroll
             for (int i = 1; i <= NO; ++i) I += O[i];
-            a = max(prm[0] - I, 0);
+            a = max(par[0] - I, 0);
         } else if (kTwo) {  // modified base stock per product
             const int IA = sum_of(X), IB = sum_of(Y);
-            const double va = posd(((double)prm[0] - IA) + posd((double)X[1] - s.mu0));
-            const double vb = posd(((double)prm[1] - IB) + posd((double)Y[1] - s.mu1));
-            aA = (int)floor(va);
-            aB = (int)floor(vb);
+            // (the integer differences are exact, and a conversion drops the fraction)
+            aA = (int)posd((double)(par[0] - IA) + posd((double)X[1] - s.mu0));
+            aB = (int)posd((double)(par[1] - IB) + posd((double)Y[1] - s.mu1));
         } else {  // (s, S) of the weekday
             const int I = sum_of(X);
-            const int lo = prm[2 * tau], hi = prm[2 * tau + 1];
+            const int lo = par[0], hi = par[1];
             a = (lo < hi && I <= lo) ? min(max(hi - I, 0), R0 - 1) : 0;
         }
 
@@ -349,7 +379,10 @@ __global__ __launch_bounds__(64) void rollout_kernel(SimDev s) {
         auto accepted = [&](int unmet) {
             int k = 0;
             if constexpr (PRE) {
-                k = __popcll(unmet >= 64 ? bits : bits & ((1ull << unmet) - 1));
+                if (BITS32)
+                    k = __popc(__builtin_amdgcn_ubfe(bits32, 0, (uint32_t)unmet));
+                else
+                    k = __popcll(unmet >= 64 ? bits : bits & ((1ull << unmet) - 1));
             } else {
                 Block bu = b0;
                 for (int i = 0; i < unmet; ++i) {
@@ -527,10 +560,19 @@ size_t sim_lds(const SimDev& s) {
 template <int FAM, int M, int LO>
 void launch_days(const SimDev& s, dim3 grid, hipStream_t st) {
     if constexpr (FAM == 1 || FAM == 3) {
-        if (s.pkpi)
-            hipLaunchKernelGGL((rollout_kernel<FAM, M, LO, true, true>), grid, dim3(64), 0, st, s);
+        const bool narrow = units_max(s, FAM) <= 31;
+        if (s.pkpi && narrow)
+            hipLaunchKernelGGL((rollout_kernel<FAM, M, LO, true, true, true>), grid, dim3(64), 0,
+                               st, s);
+        else if (s.pkpi)
+            hipLaunchKernelGGL((rollout_kernel<FAM, M, LO, true, true, false>), grid, dim3(64), 0,
+                               st, s);
+        else if (narrow)
+            hipLaunchKernelGGL((rollout_kernel<FAM, M, LO, true, false, true>), grid, dim3(64), 0,
+                               st, s);
         else
-            hipLaunchKernelGGL((rollout_kernel<FAM, M, LO, true, false>), grid, dim3(64), 0, st, s);
+            hipLaunchKernelGGL((rollout_kernel<FAM, M, LO, true, false, false>), grid, dim3(64),
+                               0, st, s);
     } else {
         hipLaunchKernelGGL((rollout_kernel<FAM, M, LO, true, false>), grid, dim3(64), 0, st, s);
     }

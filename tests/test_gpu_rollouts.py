@@ -160,6 +160,12 @@ DRAWN = {
     "A-m6-L3": (W.scenario_a(m=6, L=3, a_max=2, d_max=6), "base_stock", [[3], [0], [9]]),
     "A-m3-L2-lifo": (W.scenario_a(m=3, L=2, a_max=5, d_max=9, issuing="lifo"), "base_stock",
                      [[4], [8]]),
+    "B-31": (W.scenario_b(m=3, a_max=(4, 31), d_max=(31, 8), means=(29.0, 3.0)),
+             "mod_base_stock", [[4, 31], [0, 60], [2, 90]]),
+    "B-32": (W.scenario_b(m=3, a_max=(4, 31), d_max=(32, 8), means=(30.0, 3.0)),
+             "mod_base_stock", [[4, 31], [0, 60], [2, 90]]),
+    "B1-31": (W.scenario_b1(m=2, a_max=(6, 2), means=(1.0, 29.0), d_max=31), "mod_base_stock",
+              [[60, 2], [90, 0]]),
     "B-64": (W.scenario_b(m=2, a_max=(4, 31), d_max=(64, 8), means=(62.0, 3.0)),
              "mod_base_stock", [[4, 31], [0, 60], [2, 90]]),
     "B-65": (W.scenario_b(m=2, a_max=(4, 31), d_max=(65, 8), means=(64.0, 3.0)),
