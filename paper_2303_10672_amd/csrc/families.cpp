@@ -483,9 +483,7 @@ pvi_status tune_a(pvi_mdp* p) {
         if (e == hipSuccess) e = hipEventCreate(&e0);
         if (e == hipSuccess) e = hipEventCreate(&e1);
         if (e == hipSuccess) e = launch_fill(d.v64[0], 0.0, p->ns, s);
-        // one fixed-length sweep after another: the stop flag is never set
-        Ctl zero{};
-        if (e == hipSuccess) e = hipMemcpyAsync(d.ctl, &zero, sizeof(Ctl), hipMemcpyHostToDevice, s);
+        const Ctl zero{};  // one fixed-length sweep after another: the stop flag is never set
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         float best = 1e30f;
         std::pair<int, int> choice{p->a_G, p->a_CH};
@@ -506,10 +504,13 @@ pvi_status tune_a(pvi_mdp* p) {
             a.v_in = d.v64[0];
             a.v_out = d.v64[1];
             a.fixed = 1;
-            if ((e = launch_backup_a(a, 0, 0, 0, s)) != hipSuccess ||
+            a.span = d.span;  // sweeps as a solve runs them
+            if ((e = launch_span_init(d.span, zero, s)) != hipSuccess ||
+                (e = launch_backup_a(a, 0, 0, 0, s)) != hipSuccess ||
                 (e = hipEventRecord(e0, s)) != hipSuccess)
                 break;
-            for (int r = 0; r < 8 && e == hipSuccess; ++r) e = launch_backup_a(a, 0, 0, 0, s);
+            for (a.sweep = 1; a.sweep <= 8 && e == hipSuccess; ++a.sweep)
+                e = launch_backup_a(a, 0, 0, 0, s);
             if (e != hipSuccess || (e = hipEventRecord(e1, s)) != hipSuccess ||
                 (e = hipEventSynchronize(e1)) != hipSuccess)
                 break;

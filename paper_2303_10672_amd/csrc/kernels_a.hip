@@ -662,8 +662,8 @@ __global__ __launch_bounds__(1024) void span_kernel(Ctl* ctl, const double* part
 
 __global__ __launch_bounds__(256) void span_init_kernel(SpanBuf* b, Ctl first) {
     if (threadIdx.x == 0) b->ctl[0] = first;
-    unsigned long long* k = &b->key[0][0][0];
-    for (int i = threadIdx.x; i < 4 * kSpanSlots * 4; i += 256) k[i] = 0;
+    for (int i = threadIdx.x; i < 4 * kSpanSlots * 4; i += 256)
+        b->key[i / (4 * kSpanSlots)][i / 4 % kSpanSlots][i % 4] = 0;
 }
 
 // End of a batch of sweeps 0 .. n - 1: the last one applied, in both copies.
