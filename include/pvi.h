@@ -53,10 +53,11 @@
  *    not be used by two threads at once.  Server calls are thread-safe.
  *  - There is no CPU fallback: without a usable gfx950 device, solves return
  *    PVI_E_DEVICE.
- *  - Scenario C merges arrivals by antidiagonals for m >= 4 and up to 24 orders.  The plain
- *    merge kernels that remain elsewhere (m >= 6, or 22 orders and more) are timed at each
- *    candidate block width at the first solve of a shape (R, m, weekdays) in a process and
- *    the fastest is kept; results do not depend on the choice.  PVI_TUNE=0 in the environment
+ *  - Scenario C merges arrivals by antidiagonals for m >= 4 and up to 24 orders (the first
+ *    two merges of m >= 5 for 17 to 21; order-dependent life of m = 4 from 16).  The plain
+ *    merge kernels that remain elsewhere are timed at each candidate block width at the
+ *    first solve of a shape (R, m, weekdays) in a process and the fastest is kept; results
+ *    do not depend on the choice.  PVI_TUNE=0 in the environment
  *    skips the timing (the LDS rule then chooses); PVI_TUNE_VERBOSE=1 prints the choices to
  *    stderr; PVI_C_BLOCK=4|8|12|16|32 at mdp_create and the first solve keeps the plain
  *    kernels at that width wherever it fits (for tests).

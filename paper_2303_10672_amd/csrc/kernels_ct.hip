@@ -602,11 +602,15 @@ __global__ __launch_bounds__(256) void c_order_kernel(CDev p, const void* in_, i
     }
 }
 
+// The first two merges take this kernel for 17 to 21 orders: below, the plain fused pair is
+// faster (periodic solves of m = 5: 2.68 ms against 3.56 at 13 orders, 1.57 against 1.97 at
+// 11, while 21.5 against 31.2 the other way at 19), since a workgroup's antidiagonals no
+// longer fill its wavefronts.
 template <typename VT>
 bool c_merge23_tri_fits(const CDev& p) {
     const size_t r3 = (size_t)p.R * p.R * p.R;
     const size_t rc = c_tri_bound(p.R), rc3 = rc * rc * rc;  // LDS strides are the bound's
-    return p.m >= 5 && p.R <= 21 && 2 * rc3 * sizeof(VT) + 16 + 2 * c_tri_weights(p.R) * sizeof(double) <= (size_t)kLdsMax &&
+    return p.m >= 5 && p.R > 16 && p.R <= 21 && 2 * rc3 * sizeof(VT) + 16 + 2 * c_tri_weights(p.R) * sizeof(double) <= (size_t)kLdsMax &&
            p.nblk % (int64_t)r3 == 0 && p.R * p.nblk <= 0x1f000000 &&
            p.R * p.P * (p.nblk / (int64_t)r3) <= 0x7fffffff;
 }
@@ -624,14 +628,7 @@ hipError_t launch_merge23_tri(const CDev& p, const void* u, void* out, hipStream
     const int tasks = (2 * p.R - 1 + 64 / p.R - 1) / (64 / p.R);
     if (tasks > 16) return hipErrorInvalidConfiguration;
     const dim3 block(64 * std::max(4, tasks));
-    if (p.R <= 8)
-        hipLaunchKernelGGL((c_merge23_tri_kernel<VT, 8>), grid, block, lds, s, p, u, out);
-    else if (p.R <= 16)
-        hipLaunchKernelGGL((c_merge23_tri_kernel<VT, 16>), grid, block, lds, s, p, u, out);
-    else if (p.R <= 21)
-        hipLaunchKernelGGL((c_merge23_tri_kernel<VT, 21>), grid, block, lds, s, p, u, out);
-    else
-        return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((c_merge23_tri_kernel<VT, 21>), grid, block, lds, s, p, u, out);
     return hipGetLastError();
 }
 template hipError_t launch_merge23_tri<double>(const CDev&, const void*, void*, hipStream_t);

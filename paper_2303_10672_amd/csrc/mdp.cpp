@@ -300,8 +300,11 @@ static void build_c_tables(pvi_mdp* p) {
     for (int k = 2; k <= m; ++k)
         if (p->d.rul_c1[k - 1] != 0.0) p->c_exogenous = false;
     // the antidiagonal kernels for m >= 4 and up to 24 orders (their rows are unrolled to 24
-    // values per lane); a block width forced for tests keeps the plain ones
-    p->c_tri = m >= 4 && R <= 24 && !std::getenv("PVI_C_BLOCK");
+    // values per lane), but not for order-dependent life of m = 4 below 16 orders, where they
+    // are no faster (2.74 against 2.64 ms per solve at 11 orders; 5.95 against 6.60 at 16); a
+    // block width forced for tests keeps the plain ones
+    p->c_tri = m >= 4 && R <= 24 && (m > 4 || p->c_exogenous || R >= 16) &&
+               !std::getenv("PVI_C_BLOCK");
     p->c_lpmax = (m - 2) * (R - 1) + R;
     p->c_tab = std::max(dm + 10, R + 8 + p->c_lpmax);
     const int tab = p->c_tab;

@@ -121,6 +121,7 @@ def test_endogenous_converged(sc):
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 @pytest.mark.parametrize("m,a_max,dep", [(4, 3, 0), (4, 7, 1), (4, 8, 0), (4, 15, 1), (4, 20, 0),
                                          (4, 23, 1), (5, 4, 1), (5, 7, 0), (5, 8, 1), (5, 15, 0),
+                                         (5, 16, 0), (5, 17, 1), (5, 20, 0),
                                          (6, 4, 0), (6, 3, 1)])
 def test_antidiagonal_merges_equal_plain(monkeypatch, m, a_max, dep, prec):
     """Row bounds of 8, 16, 21 and 24 with and without a remainder, few and many rows per
