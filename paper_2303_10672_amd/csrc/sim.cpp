@@ -307,8 +307,12 @@ pvi_status run_rollouts(pvi_mdp* p, const pvi_rollout_opts* o, double* stats, do
         for (int j = 0; j < p->m - 1; ++j) per *= R0;
         d.tau0 = (int32_t)(o->start_state / per);
     }
-    // Policies of 64 rollouts side by side, where whole workgroups leave few lanes idle
-    d.by_block = (int64_t)((d.n_roll + 63) / 64) * 64 <= (int64_t)d.n_roll + d.n_roll / 8;
+    // Policies of 64 rollouts side by side, where whole workgroups leave few lanes idle and
+    // there are numbers to share.  Drawn day by day, the policies stay in the caller's order:
+    // those of a grid's low end, with the most unmet customers and the longest days, start
+    // first (144 policies of 3,000 rollouts, 70 customers: 3.3 ms, side by side 4.1)
+    d.by_block = d.dem &&
+                 (int64_t)((d.n_roll + 63) / 64) * 64 <= (int64_t)d.n_roll + d.n_roll / 8;
     if (d.dem) PVI_HIP(launch_draws(d, s));
     PVI_HIP(launch_rollouts(d, s));
     // stats[p] = (return, service, wastage, holding) x (mean, sd)
