@@ -610,7 +610,8 @@ template <typename VT>
 bool c_merge23_tri_fits(const CDev& p) {
     const size_t r3 = (size_t)p.R * p.R * p.R;
     const size_t rc = c_tri_bound(p.R), rc3 = rc * rc * rc;  // LDS strides are the bound's
-    return p.m >= 5 && p.R > 16 && p.R <= 21 && 2 * rc3 * sizeof(VT) + 16 + 2 * c_tri_weights(p.R) * sizeof(double) <= (size_t)kLdsMax &&
+    const size_t lds = 2 * rc3 * sizeof(VT) + 16 + 2 * c_tri_weights(p.R) * sizeof(double);
+    return p.m >= 5 && p.R > 16 && p.R <= 21 && lds <= (size_t)kLdsMax &&
            p.nblk % (int64_t)r3 == 0 && p.R * p.nblk <= 0x1f000000 &&
            p.R * p.P * (p.nblk / (int64_t)r3) <= 0x7fffffff;
 }

@@ -22,11 +22,11 @@
 // bounds it, 10,000 rollouts of 465 days: one table of 1,771,561 states is 157 wavefronts
 // and waits for the gather (893 us a call before, now 143 us after 49 us of draws); a grid
 // of 841 modified base-stock policies keeps the vector units full (67.3 ms before, now
-// 8.6 ms after 0.17 ms).  Where a draw depends on the order (order-dependent remaining
+// 7.4 ms after 0.17 ms).  Where a draw depends on the order (order-dependent remaining
 // life), or the numbers would not fit, each lane draws them day by day.  The loops over
-// lives are compiled for the scenarios' m and L: the general bounds (8 lives, 11 orders)
-// cost several times the work of a day with m = 3.  Floating-point contraction is
-// off so the return is the plain sum of products of the definition.
+// lives are compiled for the scenarios' m and L: with the general bounds a day walks 8 lives
+// and 11 orders whatever m and L are.  Floating-point contraction is off so the return is
+// the plain sum of products of the definition.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -152,8 +152,8 @@ def test_large_table_and_base_stock_at_the_largest_preset():
     _same(g, o.simulate("base_stock", params=grid, n_rollouts=100, seed=2))
 
 
-# On each side of the widths of a day's numbers drawn ahead (64 customers; 31 units ordered, the most there are)
-# and in each compiled life and the general one
+# On each side of the widths of a day's numbers drawn ahead (31 and 64 customers; 31 units
+# ordered, the most there are) and in each compiled life and the general one
 DRAWN = {
     "A-m1-L2": (W.scenario_a(m=1, L=2, a_max=6, d_max=9), "base_stock", [[5], [9]]),
     "A-m2": (W.scenario_a(m=2, L=1, a_max=6, d_max=9), "base_stock", [[S] for S in range(5)]),
