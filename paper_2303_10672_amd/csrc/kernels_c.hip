@@ -50,6 +50,11 @@ __device__ __forceinline__ int c_path_offset(int j, const int* Y, int m, const i
 }
 
 // U[tau][z_m..z_1]: one workgroup per (tau, z_m..z_3), lanes over (z_2, 4 of z_1).
+// A step of the walk adds one path value times four weights P(z_1 + k), which slide through
+// registers: one value and one weight read per step.  The first and last terms, whose weights
+// are F and P(D >= .), stand outside the loop; choosing each weight of each step from the
+// three tables had made the vector units the bound (266 -> 125 us at 21 orders, m = 5 and up to
+// 40 demanded; the 229 MB written take 48 us at the rate of a copy).
 template <typename VT>
 __global__ __launch_bounds__(256) void c_stage_u_kernel(CDev p) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -89,27 +94,39 @@ __global__ __launch_bounds__(256) void c_stage_u_kernel(CDev p) {
     if (tid >= R * G) return;
     const int z2 = tid / G, z1_0 = (tid - z2 * G) * J;
     const int N = b + z2;
-    const int kmax = N == 0 ? 0 : max(0, min(N, p.dmax - z1_0));
-    double acc[J] = {0.0, 0.0, 0.0, 0.0};
-    for (int k = 0; k <= kmax; ++k) {
-        const double u = S[N - k];
+    const double* r0 = p.r0 + (size_t)tau * R * p.xt + z2 + b;
+    double rew[J], acc[J], w[J];
 #pragma unroll
-        for (int i = 0; i < J; ++i) {
-            const int z1 = z1_0 + i;
-            const double w = N == 0 ? (k == 0 ? 1.0 : 0.0)
-                             : k == 0 ? sF[min(z1, p.dmax)]
-                             : k == N ? sG[z1 + N]
-                                      : sP[z1 + k];
-            acc[i] = fma(w, u, acc[i]);
+    for (int i = 0; i < J; ++i) {
+        const int z1 = min(z1_0 + i, R - 1);
+        rew[i] = r0[z1 * p.xt + z1];
+        acc[i] = fma(N == 0 ? 1.0 : sF[min(z1_0 + i, p.dmax)], S[N], 0.0);
+    }
+    const int kmax = min(N, p.dmax - z1_0), kp = min(kmax, N - 1);
+    if (kp >= 1) {
+#pragma unroll
+        for (int i = 0; i < J; ++i) w[i] = sP[z1_0 + i];
+#pragma unroll 4
+        for (int k = 1; k <= kp; ++k) {
+            const double u = S[N - k];
+#pragma unroll
+            for (int i = 0; i < J - 1; ++i) w[i] = w[i + 1];
+            w[J - 1] = sP[z1_0 + J - 1 + k];
+#pragma unroll
+            for (int i = 0; i < J; ++i) acc[i] = fma(w[i], u, acc[i]);
         }
+    }
+    if (N > 0 && kmax == N) {
+        const double u = S[0];
+#pragma unroll
+        for (int i = 0; i < J; ++i) acc[i] = fma(sG[z1_0 + i + N], u, acc[i]);
     }
     VT* U = reinterpret_cast<VT*>(p.u);
     const int64_t base = (int64_t)tile * R * R + (int64_t)z2 * R;
-    const double* r0 = p.r0 + (size_t)tau * R * p.xt;
 #pragma unroll
     for (int i = 0; i < J; ++i) {
         const int z1 = z1_0 + i;
-        if (z1 < R) U[base + z1] = (VT)(r0[z1 * p.xt + z1 + z2 + b] + p.gamma * acc[i]);
+        if (z1 < R) U[base + z1] = (VT)(rew[i] + p.gamma * acc[i]);
     }
 }
 

@@ -142,7 +142,6 @@ struct CDev {
     void* t1;
     void* tf;             // order-dependent life, plain kernels: top-level rows r = a - y_m
                           // of every a
-    double* sec;          // order-dependent life, extraction: [ns] second best so far
     const double* pmf;    // [P][tab] per-weekday demand, zero past d_max
     const double* cdf;    // [P][tab], one past d_max
     const double* tail;   // [P][tab], zero past d_max
@@ -150,19 +149,11 @@ struct CDev {
     const double* binq;   // [m][R][R] Bin(y; r, q_j) (for one order size a when the
                           // life distribution depends on it)
     const double* binm;   // [R][R] Bin(y; a, p_m(a))
-    const double* binp;   // antidiagonal kernels: the triangles of binq packed row by row,
-                          // [m][c_tri_weights(R)]
-    const double* binmp;  // and binm with rows of c_tri_bound(R), zeros past its entries
     const int32_t* pair_y;
     const int32_t* pair_r;
     const int32_t* pair_base;
     Ctl* ctl;
     int64_t nblk;         // R^(m-1) states per weekday
-    // antidiagonal kernels (tri = 1): layout of the table of level m-2, which the top level
-    // reads: stride of its rows, and of digit m-1 inside a row (R^(m-2) padded to lines)
-    int32_t tri, tlo;
-    int32_t swap23;       // 1: its lower digits come in the order x_2, x_3, x_1
-    int64_t trow;
     int64_t orow, ohi;    // a merge launch's output: stride of its rows, and of the digits
                           // above its life class
     int32_t R, m, P, nzu, npair, tab, xt, lpmax, dmax, extract;
@@ -172,6 +163,15 @@ struct CDev {
     int32_t top_only;     // and, when set, only the row r = alim - y_m
     int32_t pow_r[10];
     double gamma, cfixed;
+    double* sec;          // order-dependent life, extraction: [ns] second best so far
+    const double* binp;   // antidiagonal kernels: the triangles of binq packed row by row,
+                          // [m][c_tri_weights(R)]
+    const double* binmp;  // and binm with rows of c_tri_bound(R), zeros past its entries
+    // antidiagonal kernels (tri = 1): layout of the table of level m-2, which the top level
+    // reads: stride of its rows, and of digit m-1 inside a row (R^(m-2) padded to lines)
+    int32_t tri, tlo;
+    int32_t swap23;       // 1: its lower digits come in the order x_2, x_3, x_1
+    int64_t trow;
 };
 
 // ------------------------------------------------------------------ family B, lead time 1
