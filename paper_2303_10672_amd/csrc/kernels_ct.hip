@@ -36,7 +36,7 @@ namespace {
 typedef const __attribute__((address_space(4))) double* ConstF64;
 typedef const __attribute__((address_space(4))) int32_t* ConstI32;
 
-constexpr int kLo = 16;          // low-digit values per workgroup of c_top_kernel
+constexpr int kLo = kTopLo;      // low-digit values per workgroup of c_top_kernel
 constexpr int kTopWaves = 12;    // 4 antidiagonals of kLo values per wavefront, 2 R - 1 <= 48
 constexpr int kLdsMax = 160 * 1024;
 
@@ -170,10 +170,10 @@ __device__ __forceinline__ void tri_rows(const double (&D)[RC], const double (&W
 template <int RC, class L>
 __device__ __forceinline__ void tri_load(double (&D)[RC], int rhi, L&& load) {
 #pragma unroll
-    for (int b = 0; b < RC; b += 8)
+    for (int b = 0; b < RC; b += kTriLoad)
         if (b <= rhi) {
 #pragma unroll
-            for (int i = b; i < b + 8 && i < RC; ++i) D[i] = load(i);
+            for (int i = b; i < b + kTriLoad && i < RC; ++i) D[i] = load(i);
         }
 }
 
@@ -386,6 +386,7 @@ __global__ __launch_bounds__(64 * kTopWaves) void c_top_kernel(CDev p, const voi
     if (!EXTRACT && p.ctl->stop) return;
     constexpr int LPR = kLo * (int)sizeof(VT) / 16;  // staging lanes per row of kLo values
     constexpr int RPI = 64 / LPR;                    // rows per staging instruction
+    static_assert(RPI == c_top_rows(sizeof(VT)), "layout of the slab");
     const int R = p.R, j = p.m - 1, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
     constexpr int kRowB = kLo * (int)sizeof(VT);  // bytes of a row of the slab
@@ -435,11 +436,13 @@ __global__ __launch_bounds__(64 * kTopWaves) void c_top_kernel(CDev p, const voi
         const int t = u - ym, tb = ub - ym;  // the wavefront has tb .. tb + 3
         const int rlo = max(0, tb - (R - 1)), rhi = min(nr - 1, tb + 3);
         if (rlo <= rhi) {
-            // entry s at z = c(t - s): constant offsets but for the cap
+            // entry s at z = c(t - s): constant offsets but for the cap, and for the entries
+            // that fewer orders than RC may not have
             const int base = (ym & 1) * slabb + l * (int)sizeof(VT);
             const int get0 = base + t * kRowB, ghi = base + (R - 1) * kRowB;
             tri_load<RC>(D, rhi, [&](int s) {
-                return lds_at<VT>(smem, min(max(get0 - s * kRowB, base), ghi) + s * (RC * kRowB));
+                return lds_at<VT>(smem, min(max(get0 - s * kRowB, base), ghi) +
+                                            c_top_entry(s, R, RC) * (RC * kRowB));
             });
             const ConstF64 bmy = here_s(bm + ym * (RC + 1));  // row ym + r, entry ym
             const int nl = here_s(nr);
@@ -639,10 +642,7 @@ template <typename VT, bool EXTRACT>
 hipError_t launch_c_top(const CDev& p, const void* in, hipStream_t s) {
     const int64_t nlo = p.pow_r[p.m - 2], nlob = (nlo + kLo - 1) / kLo;
     const int64_t nslots = c_partial_slots(p.P, nlo), nwg = nlob * p.P;
-    const int rpi = 64 * 16 / (kLo * (int)sizeof(VT));
-    const size_t rows = (size_t)(p.R * c_tri_bound(p.R) + rpi - 1) / rpi * rpi;
-    const size_t lds = 2 * rows * kLo * sizeof(VT) +
-                       (size_t)p.R * kLo * (2 * sizeof(double) + sizeof(int));
+    const size_t lds = c_top_lds(p.R, sizeof(VT));
     if (p.m < 4 || p.R > 24 || !p.exogenous || lds > kLdsMax - 1024 || nslots > 0x7fffffff ||
         nwg > nslots || p.tlo % kLo != 0 || p.tlo < nlo || nlo * p.R != p.nblk)
         return hipErrorInvalidConfiguration;

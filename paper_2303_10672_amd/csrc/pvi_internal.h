@@ -8,6 +8,7 @@
 #include <string>
 #include <vector>
 
+#include "c_layout.h"
 #include "pvi.h"
 
 namespace pvi {
@@ -309,13 +310,6 @@ hipError_t launch_backup_c(const CDev& p, int storage_fp32, int extract, hipStre
 // digits per workgroup) on the handle's own tables, and write the fastest into lb.  With
 // order-independent life the top level m-1 is timed as it runs, fused with the final sum.
 hipError_t tune_c_merge(const CDev& p, hipStream_t s, int32_t lb[2][10]);
-// Compile-time bound of the antidiagonal kernels' rows for R <= 24, and the entries of one
-// level's packed weights (whole registers of 16).
-inline int c_tri_bound(int R) { return R <= 8 ? 8 : R <= 16 ? 16 : R <= 21 ? 21 : 24; }
-inline size_t c_tri_weights(int R) {
-    const int rc = c_tri_bound(R);
-    return (size_t)((rc * (rc + 1) / 2 + 15) / 16 * 16);
-}
 // The antidiagonal kernels (kernels_ct.hip): the first two merges, the top merge with the
 // final sum (order-independent life), and one order's top merge and final sum.
 template <typename VT>
