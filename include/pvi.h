@@ -274,11 +274,11 @@ pvi_status vi_solve(pvi_mdp* mdp, const pvi_solve_opts* opts, pvi_result* res);
  * allocation.  The caller brings the outputs in device memory: d_v[N_S] (FP64,
  * also the first value table of the sweeps; V_0 is written into it: zeros, or
  * opts->v0 copied from the host), d_policy[N_S] (int32) and d_gap[N_S] (FP64).
- * Everything else (control block, tables, work list, span partials and the
- * second value table) lives in a fixed device array of the library, about
- * 33 MiB per device, held until the process ends.  Limits: N_S <= 4,194,304
- * states; the handle's tables and work list within 512 KiB, its span partials
- * within 512 KiB.  Options: precision PVI_FP64, stop_rule SPAN or SUPNORM, no
+ * Everything else (control block, tables, work list and the second value table)
+ * lives in a fixed device array of the library, about 33 MiB per device, held
+ * until the process ends.  Limits: N_S <= 4,194,304 states; the handle's tables
+ * and work list (one or a few words per R^2 states, R = a_max + 1) within 512 KiB.
+ * Options: precision PVI_FP64, stop_rule SPAN or SUPNORM, no
  * checkpoint files; opts->stream (NULL: the null stream) carries every launch and
  * copy, and the call returns after synchronising it.  The kernels and their
  * order are vi_solve's, so V, policy, gap and sweep counts equal vi_solve's

@@ -1,6 +1,6 @@
 // vi_solve_noalloc: the FP64 scenario-A solve of vi_solve with no device
-// allocation.  Its working memory (control block, tables, work list, span
-// partials, the second value table) is the file-scope device array `scratch`; the
+// allocation.  Its working memory (control block with the increments' keys, tables, work
+// list, the second value table) is the file-scope device array `scratch`; the
 // caller brings the value, policy and gap outputs.  The kernels are the ones
 // vi_solve launches, in the same order, so the results are bit-identical.
 #include <hip/hip_runtime.h>
@@ -19,10 +19,9 @@ namespace {
 // Layout of the scratch array (byte offsets; every region 256-byte aligned).
 constexpr size_t kCtlBytes = (sizeof(pvi::SpanBuf) + 255) / 256 * 256;
 constexpr size_t kTableBytes = size_t(512) << 10;     // pmf, cdf, tail, r0, work list
-constexpr size_t kPartialBytes = size_t(512) << 10;   // span partials, 4 doubles each
 constexpr int64_t kMaxStates = int64_t(1) << 22;      // 4,194,304 states
 constexpr size_t kValueBytes = sizeof(double) * (size_t)kMaxStates;
-constexpr size_t kScratchBytes = kCtlBytes + kTableBytes + kPartialBytes + kValueBytes;
+constexpr size_t kScratchBytes = kCtlBytes + kTableBytes + kValueBytes;
 
 }  // namespace
 
@@ -90,10 +89,9 @@ extern "C" pvi_status vi_solve_noalloc(const pvi_mdp* cp, const pvi_solve_opts* 
                  o_r0 = o_tail + align256(tab),
                  o_grp = o_r0 + align256(sizeof(double) * p->a_r0.size()),
                  t_end = o_grp + align256(sizeof(int32_t) * p->a_groups.size());
-    const int tiles = pvi::family_tiles(p);
-    if (t_end > kTableBytes || sizeof(double) * 4 * (size_t)tiles > kPartialBytes)
-        return fail(PVI_E_INVALID, "vi_solve_noalloc: tables or work list exceed the "
-                                   "scratch limits (512 KiB each)");
+    if (t_end > kTableBytes)
+        return fail(PVI_E_INVALID, "vi_solve_noalloc: tables and work list exceed the "
+                                   "scratch limit (512 KiB)");
 
     int dev = 0;
     PVI_HIP(hipGetDevice(&dev));
@@ -107,8 +105,7 @@ extern "C" pvi_status vi_solve_noalloc(const pvi_mdp* cp, const pvi_solve_opts* 
     auto* span = reinterpret_cast<pvi::SpanBuf*>(base);
     auto* ctl = reinterpret_cast<pvi::Ctl*>(base);  // span->ctl[0]
     char* tb = base + kCtlBytes;
-    auto* partials = reinterpret_cast<double*>(base + kCtlBytes + kTableBytes);
-    auto* v_other = reinterpret_cast<double*>(base + kCtlBytes + kTableBytes + kPartialBytes);
+    auto* v_other = reinterpret_cast<double*>(base + kCtlBytes + kTableBytes);
 
     // tables and work list of this handle
     PVI_HIP(hipMemcpyAsync(tb, p->a_pmf.data(), tab, hipMemcpyHostToDevice, s));
@@ -126,7 +123,7 @@ extern "C" pvi_status vi_solve_noalloc(const pvi_mdp* cp, const pvi_solve_opts* 
     a.r0 = reinterpret_cast<const double*>(tb + o_r0);
     a.groups = reinterpret_cast<const int32_t*>(tb + o_grp);
     a.ctl = ctl;
-    a.partials = partials;
+    a.partials = nullptr;  // sweeps reduce into the SpanBuf, the extraction has none
     a.pi = d_policy;
     a.gap = d_gap;
 

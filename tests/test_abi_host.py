@@ -6,6 +6,7 @@ import struct
 
 import numpy as np
 import pytest
+import torch
 
 import workloads as W
 from oracle.oracle import Oracle, life_probabilities
@@ -331,3 +332,31 @@ def test_scenario_c_beyond_2_31_states_serves_heuristic_rollouts_only():
     assert "2^31" in pvi._lib.pvi_last_error().decode()
     with pytest.raises(pvi.PviError, match="2\\^31"):
         pvi.mdp_create(W.scenario_a(m=5, L=4, a_max=20, d_max=30))   # 21^8 states
+
+
+@pytest.mark.skipif(torch.cuda.device_count() > 0, reason="passes addresses that a device would use")
+@pytest.mark.parametrize("issuing", ["fifo", "lifo"])
+def test_noalloc_serves_every_small_work_list(issuing):
+    """vi_solve_noalloc within its documented limits: no shape of up to 4,194,304 states whose
+    tiles, one per R^2 states (R with m = 1), need a work list well inside 512 KiB is refused
+    before the device (absent here); one whose list cannot fit is."""
+    inval, device = [], 0
+    for a_max in range(32):
+        R = a_max + 1
+        for m in range(1, 9):
+            for L in range(1, 13 - m):
+                tiles = R ** (m + L - (3 if m >= 2 else 2))
+                if R ** (m + L - 1) > 4194304 or tiles > 100_000:
+                    continue
+                h = pvi.mdp_create(W.scenario_a(m=m, L=L, a_max=a_max, d_max=20, issuing=issuing))
+                try:
+                    pvi.vi_solve_noalloc(h, 1 << 20, 1 << 20, 1 << 20)
+                except pvi.PviError as e:
+                    (inval.append((R, m, L, tiles)) if e.status == pvi.PVI_E_INVALID else None)
+                    device += e.status == pvi.PVI_E_DEVICE
+    assert not inval, inval
+    assert device > 600
+    h = pvi.mdp_create(W.scenario_a(m=1, L=10, a_max=3, d_max=20, issuing=issuing))  # 262,144 tiles
+    with pytest.raises(pvi.PviError, match="scratch limit") as e:
+        pvi.vi_solve_noalloc(h, 1 << 20, 1 << 20, 1 << 20)
+    assert e.value.status == pvi.PVI_E_INVALID

@@ -125,3 +125,13 @@ def test_large_results_reach_the_host_whole(m, L, a_max):
     pinned = torch.empty(n, dtype=torch.float64).pin_memory().numpy()
     pvi._check(pvi._lib.value_get(h.handle, pvi._dptr(pinned)), "value_get")
     assert np.array_equal(pinned, V)
+
+
+@pytest.mark.parametrize("m,L,a_max,issuing", [
+    (5, 2, 11, "fifo"), (6, 2, 6, "fifo"), (8, 4, 2, "fifo"), (1, 5, 15, "fifo"),
+    (3, 4, 11, "lifo"), (1, 5, 11, "lifo")])
+def test_many_tiles(m, L, a_max, issuing):
+    """The shapes with the most tiles per state: 16,807 to 65,536 of them."""
+    sc = W.scenario_a(m=m, L=L, a_max=a_max, d_max=30, issuing=issuing)
+    v0 = W.random_values((a_max + 1) ** (m + L - 1), seed=m)
+    same(solve_noalloc(sc, v0=v0, fixed_sweeps=3), solve_alloc(sc, v0=v0, fixed_sweeps=3))
