@@ -748,6 +748,12 @@ static hipError_t launch_a_t(const ADev& p, hipStream_t s, hipEvent_t ev0, hipEv
     if (p.R == 21) return launch_a_r<VT, KAHAN, EXTRACT, 21, true>(p, s, ev0, ev1);
     if (p.R <= 8) return launch_a_r<VT, KAHAN, EXTRACT, 8>(p, s, ev0, ev1);
     if (p.R <= 16) return launch_a_r<VT, KAHAN, EXTRACT, 16>(p, s, ev0, ev1);
+    // 17 to 20 orders, one tile per wavefront: rows of 21 give a state three lanes of seven
+    // actions (60 of 64 lanes at 20 orders), rows of 24 two of twelve (40 lanes).  Us per FP64
+    // sweep, 24 and 21: 43.2 and 34.4 at 20^5 states with m = 2, 49.7 and 41.2 with m = 3, 516
+    // and 411 at 17^6 with m = 5 (whole tiles in rows of 24: 45.1, 56.3 and 482)
+    if (p.R <= 21 && p.G == 1)
+        return launch_a_g<VT, KAHAN, EXTRACT, 21, false, Row<VT, 21>::kGroups>(p, s, ev0, ev1);
     if (p.R <= 24) return launch_a_r<VT, KAHAN, EXTRACT, 24>(p, s, ev0, ev1);
     if (p.R <= 32) return launch_a_r<VT, KAHAN, EXTRACT, 32>(p, s, ev0, ev1);
     return hipErrorInvalidValue;

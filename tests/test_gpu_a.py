@@ -246,3 +246,19 @@ def test_actions_split_over_lanes_equal_whole_tiles(sc, monkeypatch):
     for other in runs[1:]:
         for x, y in zip(runs[0], other):
             assert np.array_equal(x, y)
+
+
+# 17 to 20 orders take the split kernel of 21: (1, 2) has one life class, (3, 1) rows in parts
+@pytest.mark.parametrize("m,L", [(1, 2), (2, 2), (3, 1)])
+@pytest.mark.parametrize("R", [18, 19, 20])
+def test_rows_of_21_serve_fewer_orders(R, m, L, monkeypatch):
+    sc = W.scenario_a(m=m, L=L, a_max=R - 1, d_max=20, demand={
+        "kind": "gamma", "mean": [0.4 * R + 1.0], "cv": [0.8]})
+    test_actions_split_over_lanes_equal_whole_tiles(sc, monkeypatch)
+    o = Oracle(sc)
+    V = W.random_values(o.n_states, seed=11)
+    _, pi, gap = o.sweep(V)[:3]
+    monkeypatch.setenv("PVI_A_GROUP", "1")
+    out = pvi.vi_backup(pvi.mdp_create(sc), V)
+    clear = gap > 1e-9 * np.abs(V).max()
+    assert np.array_equal(out[1][clear], pi[clear])
