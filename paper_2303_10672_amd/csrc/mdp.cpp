@@ -34,17 +34,31 @@ static int64_t ipow_i(int64_t b, int e) {
 // (X_1, total stock) for FIFO or (X_1, X_2 + ... + X_m) for LIFO:
 // sum_d P(d) (-C_h [X - d - W]^+ - C_s [d - X]^+ - C_w W) with W from the FIFO or
 // LIFO issuing equation (Appendix A, reward equation).
+// Whether the scenario-A backup packs floor(64 / R) tiles into a wavefront where nothing is
+// timed (vi_solve_noalloc on a fresh handle, PVI_TUNE=0); one tile per wavefront otherwise.
+// Packing loses the lanes that share a state and wins back the part of a wavefront's work
+// that does not depend on its tiles, so it pays for many tiles, for few steps per tile
+// (m = 1: one) and for few actions per state.  Us per FP64 sweep, one tile and packed:
+// m = 1: 6.7 and 7.1 with 1,728 tiles (12 orders), 7.5 and 7.2 with 2,197 (13 orders), 23.6
+// and 13.6 with 20,736.  Up to 11 orders: 19.4 and 20.9 with 6,561 tiles (9^6, m = 5), 24.7
+// and 24.1 with 10,000 (10^6, m = 5), 26.8 and 18.2 with 16,807 (7^7).  12 to 16 orders, with
+// 20,736 tiles: 47.5 and 43.4 at m = 4, but 53.5 and 58.1 at m = 5.  More orders never: 44.4
+// and 65.3 at 20^5, m = 4.
+static bool a_pack(const pvi_mdp* p, int64_t tiles) {
+    const int R = p->rad[0];
+    if (p->m == 1) return tiles >= 2048;
+    return tiles >= 7000 && (R <= 11 || (R <= 16 && p->m <= 4));
+}
+
 // Work list of the scenario-A backup kernel for G tiles per wavefront (0: the rule
 // below) and CH path points per staged chunk (0: as many as the staging lanes allow).
 // One wavefront takes G tiles of equal digit sum b (so their loops run in lockstep),
 // R lanes each; a wavefront of one tile (G = 1) splits each state's actions over several
 // lanes instead.  Tiles are grouped per block of G in-transit vectors and, inside one
 // digit sum, by (X_m..X_3) then in-transit vector, so a full group is one (X_m..X_3)
-// over G in-transit vectors.  The rule: G = 1, but floor(64 / R) for up to 11 orders where
-// that still gives two wavefronts per SIMD (2,048; 26 against 49 us per sweep at 8^7 states,
-// 29.7 against 31.3 at 11^6, while 8.5 against 13.2 us the other way at 11^5 and 53 against
-// 58 us at 21^5).  The autotuner (families.cpp) times both for the larger instances
-// at the first solve of a shape.  Results do not depend on G or CH (each
+// over G in-transit vectors.  The rule is a_pack's; the autotuner (families.cpp) times both
+// forms for the larger instances at the first solve of a shape.  Results do not depend on G
+// or CH (each
 // lane's arithmetic is its own tile's).  PVI_A_GROUP=<G> (1 .. floor(64 / R)) and
 // PVI_A_CHUNK=<CH> fix them, for tests.
 void build_a_work_list(pvi_mdp* p, int G_req, int CH_req) {
@@ -54,7 +68,7 @@ void build_a_work_list(pvi_mdp* p, int G_req, int CH_req) {
     const int64_t nzt = p->m >= 2 ? (int64_t)ipow_i(R, p->m - 2) : 1;
     const int gmax = a_group_max(p);
     p->a_G = G_req > 0 ? std::min(G_req, gmax)
-                       : (R <= 11 && nh * nzt / gmax >= 2048 ? gmax : 1);
+                       : (a_pack(p, nh * nzt) ? gmax : 1);
     if (const char* force = std::getenv("PVI_A_GROUP")) {
         const int g = std::atoi(force);
         if (g >= 1 && g <= gmax) p->a_G = g;
