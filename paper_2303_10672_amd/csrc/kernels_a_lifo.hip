@@ -141,7 +141,10 @@ __global__ __launch_bounds__(1024) void backup_a_lifo_kernel(ADev p) {
         // (threads past the last state repeat it)
         if (tid < RR) reinterpret_cast<VT*>(p.v_out)[s_idx] = o;
         const double out = (double)o, dv = out - old;
-        double dmx = dv, dmn = dv, vmx = out, vmn = out;
+        // (a NaN increment, from a caller's V_0 that holds one, is passed over: as a key it
+        // would stand above every number of its slot)
+        double dmx = fmax(dv, -DBL_MAX), dmn = fmin(dv, DBL_MAX);
+        double vmx = fmax(out, -DBL_MAX), vmn = fmin(out, DBL_MAX);
         if (p.span) {
             dmx = wave_max(dmx);
             dmn = wave_min(dmn);

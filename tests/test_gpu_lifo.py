@@ -156,3 +156,31 @@ def test_lifo_lists_longer_than_a_request(sc):
     clear = gapo > 1e-9
     assert np.array_equal(pig[clear], pio[clear])
     assert np.allclose(gapg[clear], gapo[clear], rtol=1e-8, atol=1e-8)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_wide"])
+@pytest.mark.parametrize("m,L,a_max", [(3, 2, 10), (2, 3, 10), (4, 2, 4)])
+def test_nan_increments_are_passed_over(m, L, a_max, precision):
+    """A V_0 with NaN for every state whose newest order in transit is a_max: increments of
+    those states are NaN, and max and min of the sweep are those of the other states, whose
+    wavefronts share the reduction's slots with them.  The largest and the smallest increment
+    are put into one tile after the other."""
+    R = a_max + 1
+    sc = W.scenario_a(m=m, L=L, a_max=a_max, d_max=12, issuing="lifo")
+    n, block = R ** (m + L - 1), R ** (m + L - 2)
+    base = W.random_values(n, seed=5)
+    base[(R - 1) * block:] = np.nan
+    h = pvi.mdp_create(sc)
+    # one state per tile (O, X_{m-1}..X_2) of the finite part: X_m = 0, X_1 = 1
+    tiles = [o * R ** m + z * R + 1 for o in range(R ** (L - 1)) for z in range(R ** (m - 2))]
+    tiles = [s for s in tiles if s < (R - 1) * block]
+    for s in tiles[::max(1, len(tiles) // 24)]:
+        v0 = base.copy()
+        v0[s] -= 1000.0
+        v0[s - 1] += 1000.0
+        r = pvi.vi_solve(h, precision=precision, v0=v0, fixed_sweeps=1)
+        dv = pvi.value_get(h) - v0
+        # FP32 storage: two roundings of centred values below 2,048 (half an ulp is 2^-14)
+        tol = 0.0 if precision == "fp64" else 4 * 2.0 ** -14
+        assert abs(r["dmax"] - np.nanmax(dv)) <= tol
+        assert abs(r["dmin"] - np.nanmin(dv)) <= tol
