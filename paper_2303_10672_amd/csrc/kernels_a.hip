@@ -114,11 +114,13 @@ __host__ __device__ constexpr int best_size(int n, bool extract) {
 // Value staged for the padding actions R <= a < RC: so negative that their Q never wins
 // the max, small enough that weighted sums of it (total weight <= 1) stay finite.  With it
 // the action loops need no bound check.  Variants compiled for one exact action count
-// (EXACT) need it only where the split kernel's last lanes overhang the row.
-template <typename VT>
-__device__ constexpr VT kPadValue = VT(-1e30);
-template <>
-__device__ constexpr double kPadValue<double> = -1e300;
+// (EXACT) need one only where the split kernel's last lanes overhang the row (11 orders, four
+// lanes of three); there it is NaN, which no maximum and no comparison takes, so that values
+// below -1e300, infinite values and NaN in V give what whole rows of 11 give.
+template <typename VT, bool EXACT>
+__device__ constexpr VT kPadValue = EXACT        ? VT(__builtin_nan(""))
+                                    : sizeof(VT) == 8 ? VT(-1e300)
+                                                      : VT(-1e30);
 
 // A weight: its product is rounded before a difference of weights is formed.
 __device__ __forceinline__ double weight(double gamma, double prob) {
@@ -296,7 +298,7 @@ __device__ __forceinline__ void backup_a_body(ADev p, unsigned char* smem) {
 #pragma unroll
             for (int e = 0; e < SPL; ++e) {
                 const bool sure = EXACT && (AG == 1 || (NSPLIT - 1) * SPL + e < RC);
-                v[e] = sure || sh * SPL + e < R ? pre[e] : kPadValue<VT>;
+                v[e] = sure || sh * SPL + e < R ? pre[e] : kPadValue<VT, EXACT>;
             }
             if constexpr (SPL % W == 0) {
                 VV* d = reinterpret_cast<VV*>(dst);

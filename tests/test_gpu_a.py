@@ -262,3 +262,23 @@ def test_rows_of_21_serve_fewer_orders(R, m, L, monkeypatch):
     out = pvi.vi_backup(pvi.mdp_create(sc), V)
     clear = gap > 1e-9 * np.abs(V).max()
     assert np.array_equal(out[1][clear], pi[clear])
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf, -1e301])
+@pytest.mark.parametrize("m,L", [(1, 2), (3, 2)])
+def test_values_that_are_no_numbers_split_over_lanes(m, L, value, monkeypatch):
+    """11 orders, four lanes of three actions: the twelfth is no action whatever V holds.  The
+    packed kernel, compiled for 11 actions, has no padding."""
+    n = 11 ** (m + L - 1)
+    rng = np.random.default_rng(m)
+    for share in (0.02, 0.5, 1.0):
+        V = W.random_values(n, seed=2)
+        V[rng.random(n) < share] = value
+        runs = []
+        for G in (1, 2):
+            monkeypatch.setenv("PVI_A_GROUP", str(G))
+            h = pvi.mdp_create(W.scenario_a(m=m, L=L, a_max=10, d_max=15))
+            runs.append([x for prec in ("fp64", "fp32", "fp32_wide")
+                         for x in pvi.vi_backup(h, V, prec)])
+        for x, y in zip(*runs):
+            assert np.array_equal(x, y, equal_nan=x.dtype == np.float64)
