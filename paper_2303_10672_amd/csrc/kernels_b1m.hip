@@ -113,8 +113,10 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_stage_w_kernel(B1Dev p) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int xr = 16 * mt + kk + 4 * r;
+                // no stock of b: an empty sum (its weight 0 times an infinite value is none)
                 if (xr < p.Rb)
-                    p.w[((int64_t)(y * p.Rb + xr) * p.na1 + g) * p.nap + t * kRow + col] = acc[r];
+                    p.w[((int64_t)(y * p.Rb + xr) * p.na1 + g) * p.nap + t * kRow + col] =
+                        y + xr > 0 ? acc[r] : 0.0;
             }
         }
     }

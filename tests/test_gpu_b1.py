@@ -166,6 +166,26 @@ def test_matrix_kernels_agree_with_general(monkeypatch, m, a_max, prec):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf, 1.7e308, -1.7e308])
+@pytest.mark.parametrize("m,a_max", [(1, (5, 6)), (2, (15, 15)), (2, (19, 9)), (3, (4, 5))],
+                         ids=str)
+def test_matrix_kernels_agree_where_values_are_no_numbers(monkeypatch, m, a_max, value):
+    """Padding (of orders, of path points, of X_1) and empty sums add nothing, whatever V
+    holds."""
+    sc = W.scenario_b1(m=m, a_max=a_max, means=(3.0, 3.0))
+    h = pvi.mdp_create(sc)
+    rng = np.random.default_rng(m)
+    for share in (0.02, 0.5, 1.0):
+        V = W.random_values(h.n_states, seed=2)
+        V[rng.random(h.n_states) < share] = value
+        got = []
+        for env in ("1", "0"):
+            monkeypatch.setenv("PVI_B1_LANES", env)
+            got.append([x for prec in ("fp64", "fp32") for x in pvi.vi_backup(h, V, prec)])
+        for a, b in zip(*got):
+            assert np.array_equal(a, b, equal_nan=a.dtype == np.float64)
+
+
 def test_rollouts_match_oracle():
     sc = W.scenario_b1(m=2, a_max=(5, 4), means=(3.0, 2.0), rho=0.6, d_max=12)
     o = Oracle(sc)
