@@ -220,6 +220,27 @@ static size_t c_table_entries(const pvi_mdp* p) {  // entries of one merge table
     return (size_t)p->P * p->c_npair * row;
 }
 
+// Entries of the merge tables t0 and t1 (level j of the chain is written to t_{j mod 2}) and
+// of the third one.  The antidiagonal kernels write level m-2 and no more: with m = 4 that is
+// level 2 alone, in t0; with m = 5 and the first two merges in one kernel it is level 3 alone,
+// in t1.  Their third table holds the second best value of a state (order-dependent life).
+static void c_tables(const pvi_mdp* p, size_t (&n)[3]) {
+    const size_t tt = p->m >= 3 ? c_table_entries(p) : 0;
+    n[0] = make_cdev(p).swap23 ? 0 : tt;
+    n[1] = p->c_tri && p->m == 4 ? 0 : tt;
+    n[2] = p->c_exogenous ? 0 : p->c_tri ? (size_t)p->ns : tt;
+}
+
+// Entries of their packed weights, and of Bin(y; a, p_m) in padded rows.
+static size_t c_packed_weights(const pvi_mdp* p) {
+    const size_t R = (size_t)p->rad[0];
+    return p->c_tri ? p->c_binq.size() / (R * R) * c_tri_weights((int)R) : 1;
+}
+static size_t c_padded_rows(const pvi_mdp* p) {
+    const size_t rc = (size_t)c_tri_bound(p->rad[0]);
+    return (2 * rc + 1) * rc;
+}
+
 std::string family_support_msg(const pvi_mdp* p) {
     if (p->family == PVI_FAMILY_LEADTIME) return "ok";
     if (p->family == PVI_FAMILY_SUBST2) {
@@ -294,10 +315,11 @@ size_t family_extra_bytes(const pvi_mdp* p) {
                                  p->b_ppad.size() + p->b_gpad.size());
     if (p->family == PVI_FAMILY_RUL_WEEKDAY) {
         const size_t ut = (size_t)p->ns * p->rad[0];
-        const size_t tt = p->m >= 3 ? c_table_entries(p) : 0;
-        const size_t ntab = p->c_exogenous ? 2 : 3;
-        return sizeof(double) * (ut + ntab * tt + 3 * p->c_pmf.size() + p->c_r0.size() +
-                                 5 * p->c_binq.size() + p->c_binm.size() + 2080);
+        size_t tab[3];
+        c_tables(p, tab);
+        return sizeof(double) * (ut + tab[0] + tab[1] + tab[2] + 3 * p->c_pmf.size() +
+                                 p->c_r0.size() + p->c_binq.size() + p->c_binm.size() +
+                                 c_packed_weights(p) + c_padded_rows(p));
     }
     if (p->family == PVI_FAMILY_SUBST2_L1)
         return sizeof(double) * (b1_w_entries(p) + b1_y_entries(p) + 3 * p->b1_pa1.size() +
@@ -574,13 +596,13 @@ pvi_status family_init(pvi_mdp* p) {
     }
     if (p->family == PVI_FAMILY_RUL_WEEKDAY) {
         const size_t ut = (size_t)p->ns * p->rad[0];
-        const size_t tt = p->m >= 3 ? c_table_entries(p) : 1;
-        const size_t tft = p->c_tri ? (size_t)p->ns : tt;
+        size_t tab[3];
+        c_tables(p, tab);
+        for (size_t& n : tab) n = std::max<size_t>(n, 1);
         // their weights: each level's triangle packed, and Bin(y; a, p_m) in padded rows
         const int R = p->rad[0], rc = c_tri_bound(R);
         const size_t nlev = p->c_binq.size() / ((size_t)R * R), nw = c_tri_weights(R);
-        std::vector<double> binp(p->c_tri ? nlev * nw : 1, 0.0),
-            binmp((size_t)(2 * rc + 1) * rc, 0.0);
+        std::vector<double> binp(c_packed_weights(p), 0.0), binmp(c_padded_rows(p), 0.0);
         for (int r = 0; r < R && p->c_tri; ++r)
             for (int y = 0; y <= r; ++y) {
                 for (size_t b = 0; b < nlev; ++b)
@@ -588,9 +610,9 @@ pvi_status family_init(pvi_mdp* p) {
                 binmp[(size_t)r * rc + y] = p->c_binm[(size_t)r * R + y];
             }
         if (hipMalloc(&d.cu, sizeof(double) * ut) != hipSuccess ||
-            hipMalloc(&d.ct0, sizeof(double) * tt) != hipSuccess ||
-            hipMalloc(&d.ct1, sizeof(double) * tt) != hipSuccess ||
-            (!p->c_exogenous && hipMalloc(&d.ctf, sizeof(double) * tft) != hipSuccess) ||
+            hipMalloc(&d.ct0, sizeof(double) * tab[0]) != hipSuccess ||
+            hipMalloc(&d.ct1, sizeof(double) * tab[1]) != hipSuccess ||
+            (!p->c_exogenous && hipMalloc(&d.ctf, sizeof(double) * tab[2]) != hipSuccess) ||
             upload_vec(&d.cpmf, p->c_pmf) != hipSuccess ||
             upload_vec(&d.ccdf, p->c_cdf) != hipSuccess ||
             upload_vec(&d.ctail, p->c_tail) != hipSuccess ||

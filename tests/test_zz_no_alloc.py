@@ -135,3 +135,38 @@ def test_many_tiles(m, L, a_max, issuing):
     sc = W.scenario_a(m=m, L=L, a_max=a_max, d_max=30, issuing=issuing)
     v0 = W.random_values((a_max + 1) ** (m + L - 1), seed=m)
     same(solve_noalloc(sc, v0=v0, fixed_sweeps=3), solve_alloc(sc, v0=v0, fixed_sweeps=3))
+
+
+MEMORY = {
+    "C m=5 R=19": W.scenario_c(m=5, a_max=18, d_max=20, c0=[0.0, 1.0, 0.5, 0.7, 0.3]),
+    "C m=5 R=17 order": W.scenario_c(m=5, a_max=16, d_max=20, c0=[0.0, 1.0, 0.5, 0.7, 0.3],
+                                     c1=[0.0, 0.1, 0.2, 0.15, 0.05]),
+    "C m=5 R=11": W.scenario_c(m=5, a_max=10, d_max=20, c0=[0.0, 1.0, 0.5, 0.7, 0.3]),
+    "C m=4 R=24": W.scenario_c(m=4, a_max=23, d_max=20, c0=[0.0, 1.0, 0.5, 0.7]),
+    "C m=4 R=24 order": W.scenario_c(m=4, a_max=23, d_max=20, c0=[0.0, 1.0, 0.5, 0.7],
+                                     c1=[0.0, 0.1, 0.2, 0.15]),
+    "A": W.config1(),
+    "B1": W.scenario_b1(m=3, a_max=(9, 11), means=(3.0, 3.0)),
+}
+
+
+@pytest.mark.parametrize("name", list(MEMORY))
+def test_memory_asked_for_is_the_memory_used(name):
+    """A request is admitted by the bytes its solve takes: neither fewer nor much more.  Each of
+    a handle's allocations (about 30) is rounded up to 2 MiB at most."""
+    sc = MEMORY[name]
+    rule = "periodic" if sc["family"] == "C" else "span"
+    h = pvi.mdp_create(sc)
+    pvi.vi_solve(pvi.mdp_create(W.config0()))            # the runtime's own memory
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    pvi.vi_solve(h, precision="fp64", stop_rule=rule, max_sweeps=9, allow_not_converged=True)
+    used = free - torch.cuda.mem_get_info()[0]
+    s = pvi.Server()
+    try:
+        (t,) = s.submit([pvi.mdp_create(sc)], precision="fp64", max_sweeps=1, stop_rule=rule)
+        asked = s.ticket_info(t)["bytes"]
+        s.wait(t)
+    finally:
+        s.close()
+    assert abs(asked - used) <= 64 << 20, (asked, used)
