@@ -7,13 +7,19 @@
 namespace pvi {
 
 // Compile-time bound of the kernels' rows for R <= 24 orders, and the entries of one level's
-// packed weights (whole registers of 16).
-constexpr int c_tri_bound(int R) { return R <= 8 ? 8 : R <= 16 ? 16 : R <= 21 ? 21 : 24; }
+// packed weights (whole registers of 16).  A slab's rows and reads go by the bound, so 9 to 12
+// orders have one of their own: FP64 sweeps of m = 6 with rows of 16 and of 12 take 258 and
+// 229 us at 9 orders (the plain kernels 233), 842 and 788 at 11 (797).
+constexpr int c_tri_bound(int R) {
+    return R <= 8 ? 8 : R <= 12 ? 12 : R <= 16 ? 16 : R <= 21 ? 21 : 24;
+}
 constexpr size_t c_tri_weights(int R) {
     return (size_t)((c_tri_bound(R) * (c_tri_bound(R) + 1) / 2 + 15) / 16 * 16);
 }
 // The fewest orders whose rows have the bound rc.
-constexpr int c_tri_least(int rc) { return rc == 8 ? 1 : rc == 16 ? 9 : rc == 21 ? 17 : 22; }
+constexpr int c_tri_least(int rc) {
+    return rc == 8 ? 1 : rc == 12 ? 9 : rc == 16 ? 13 : rc == 21 ? 17 : 22;
+}
 
 // The vectors D[s] of a lane are loaded eight entries at a time (kTriLoad), so entries
 // s >= R are loaded too; no row that exists uses them.  A slab holds R of them, with rows of

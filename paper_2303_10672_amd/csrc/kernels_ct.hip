@@ -650,6 +650,8 @@ hipError_t launch_c_top(const CDev& p, const void* in, hipStream_t s) {
     const int ns = (int)nslots;
     if (p.R <= 8)
         hipLaunchKernelGGL((c_top_kernel<VT, 8, EXTRACT>), grid, block, lds, s, p, in, ns);
+    else if (p.R <= 12)
+        hipLaunchKernelGGL((c_top_kernel<VT, 12, EXTRACT>), grid, block, lds, s, p, in, ns);
     else if (p.R <= 16)
         hipLaunchKernelGGL((c_top_kernel<VT, 16, EXTRACT>), grid, block, lds, s, p, in, ns);
     else if (p.R <= 21)

@@ -141,3 +141,11 @@ def test_antidiagonal_merges_equal_plain(monkeypatch, m, a_max, dep, prec):
         got.append((pvi.value_get(h),) + pvi.policy_get(h))
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("m,a_max", [(4, 11), (4, 12), (5, 9), (5, 11), (6, 8)])
+def test_row_bound_of_12(monkeypatch, m, a_max):
+    """9 to 12 orders, and 13 beside them, order-independent life."""
+    for prec in ("fp64", "fp32"):
+        test_antidiagonal_merges_equal_plain(monkeypatch, m, a_max, 0, prec)
+        monkeypatch.delenv("PVI_C_BLOCK")
