@@ -62,9 +62,10 @@
  *    stderr; PVI_C_BLOCK=4|8|12|16|32 at mdp_create and the first solve keeps the plain
  *    kernels at that width wherever it fits (for tests).
  *  - Scenario A (FIFO) gives a wavefront one tile and splits the actions of its states
- *    over its lanes, or packs floor(64 / R) tiles into it where that is faster (up to 11
- *    orders and many states); results do not depend on the choice.  PVI_A_GROUP=<G>, 1 <= G <= floor(64 / R), read by mdp_create,
- *    fixes it (for tests).
+ *    over its lanes, or packs floor(64 / R) tiles into it where that is faster (many
+ *    tiles of few orders); above 1,024 tiles vi_solve times both at the first solve of a
+ *    shape.  Results do not depend on the choice.  PVI_A_GROUP=<G>,
+ *    1 <= G <= floor(64 / R), read by mdp_create, fixes it (for tests).
  *  - Scenario B as the paper runs it (lead time 1) sums on the FP64 matrix cores for up
  *    to 32 orders of each product; PVI_B1_LANES=0 keeps the general kernels (for tests:
  *    both give the same values).
@@ -447,7 +448,13 @@ typedef struct pvi_rollout_opts {
  * Errors: PVI_E_INVALID (options, a kind that does not suit the family, table
  * entries out of range, per-product outputs for one product), PVI_E_NOT_READY
  * (TABLE with NULL table before any solve), PVI_E_NOMEM, PVI_E_DEVICE.  Device
- * buffers are taken and released within the call. */
+ * buffers are taken and released within the call: the results (32 bytes per rollout,
+ * 80 with per-product KPIs), the caller's table, and the days' random numbers, drawn
+ * ahead once for all policies, per rollout and day 4 bytes (two products 12, scenario C
+ * 4 + 4 m).  At most 1 GiB goes to those: a call that needs more, or whose allocation
+ * of them fails, and one whose draws depend on the orders draws them day by day, with
+ * the same results.  A request server on the device sees that memory as taken while
+ * the call runs. */
 pvi_status policy_rollouts(pvi_mdp* mdp, const pvi_rollout_opts* opts, double* stats,
                            double* returns, double* kpis);
 

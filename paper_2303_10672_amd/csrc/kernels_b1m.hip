@@ -396,7 +396,7 @@ __global__ __launch_bounds__(64 * kWaves) void b1m_final_kernel(B1Dev p) {
 #pragma unroll
                     for (int i = 0; i < XB; ++i) {
                         double q = fma(p.gamma, acc[i][mt][r] + y[gi & 1][mt][r], base);
-                    if constexpr (EXTRACT) {
+                        if constexpr (EXTRACT) {
                             if (!real) q = -DBL_MAX;  // also where values are infinite
                             if (q > best[gi][i][mt][r]) {
                                 second[gi][i][mt][r] = best[gi][i][mt][r];

@@ -118,9 +118,10 @@ __host__ __device__ __forceinline__ int units_max(const SimDev& s, int family) {
 }
 
 // The numbers of one (rollout, day), which no policy changes: the demands of both products
-// in the halves of `dem`; bit i of `bits` (32-bit words for up to 31 customers) is whether the i-th unmet customer accepts
-// substitution (two products), and scenario C's `life` has a word per remaining life k - 1,
-// bit i set when the i-th unit ordered arrives with life k (life independent of the order).
+// in the halves of `dem`; bit i of `bits` (32-bit words for up to 31 customers) is whether
+// the i-th unmet customer accepts substitution (two products), and scenario C's `life` has a
+// word per remaining life k - 1, bit i set when the i-th unit ordered arrives with life k
+// (life independent of the order).
 // One thread per (rollout, day); [day][rollout], so a wavefront of rollouts reads lines.
 // Bounded by Philox's 64-bit multiplies (4.65 million days in 49 us; 20 MB written).
 template <int FAM>

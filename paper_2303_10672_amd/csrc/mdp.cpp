@@ -30,10 +30,6 @@ static int64_t ipow_i(int64_t b, int e) {
     return r;
 }
 
-// Scenario A expected one-day reward without the order cost, as a table over
-// (X_1, total stock) for FIFO or (X_1, X_2 + ... + X_m) for LIFO:
-// sum_d P(d) (-C_h [X - d - W]^+ - C_s [d - X]^+ - C_w W) with W from the FIFO or
-// LIFO issuing equation (Appendix A, reward equation).
 // Whether the scenario-A backup packs floor(64 / R) tiles into a wavefront where nothing is
 // timed (vi_solve_noalloc on a fresh handle, PVI_TUNE=0); one tile per wavefront otherwise.
 // Packing loses the lanes that share a state and wins back the part of a wavefront's work
@@ -58,9 +54,8 @@ static bool a_pack(const pvi_mdp* p, int64_t tiles) {
 // digit sum, by (X_m..X_3) then in-transit vector, so a full group is one (X_m..X_3)
 // over G in-transit vectors.  The rule is a_pack's; the autotuner (families.cpp) times both
 // forms for the larger instances at the first solve of a shape.  Results do not depend on G
-// or CH (each
-// lane's arithmetic is its own tile's).  PVI_A_GROUP=<G> (1 .. floor(64 / R)) and
-// PVI_A_CHUNK=<CH> fix them, for tests.
+// or CH (each lane's arithmetic is its own tile's).  PVI_A_GROUP=<G> (1 .. floor(64 / R))
+// and PVI_A_CHUNK=<CH> fix them, for tests.
 void build_a_work_list(pvi_mdp* p, int G_req, int CH_req) {
     const int R = p->rad[0];
     int64_t nh = 1;
@@ -135,14 +130,18 @@ void build_a_work_list(pvi_mdp* p, int G_req, int CH_req) {
 
 int a_group_max(const pvi_mdp* p) { return std::min(16, std::max(1, 64 / p->rad[0])); }
 
-// The kernel stages each path point with one lane per 8 actions (R = 11 and 21: per 6 and
-// 7): CH points per chunk of G tiles fill <= 64 lanes.
+// The kernel stages each path point with one lane per 8 actions (11 orders: per 6; 17 to 21:
+// per 7 with one tile per wavefront): CH points per chunk of G tiles fill <= 64 lanes.
 int a_chunk_max(const pvi_mdp* p, int G) {
     const int R = p->rad[0];
     const int rmax = R <= 8 ? 8 : R <= 16 ? 16 : R <= 24 ? 24 : 32;
     return std::max(1, 64 / ((rmax / 8) * G));
 }
 
+// Scenario A tables: padded demand, and the expected one-day reward without the order
+// cost over (X_1, total stock) for FIFO or (X_1, X_2 + ... + X_m) for LIFO:
+// sum_d P(d) (-C_h [X - d - W]^+ - C_s [d - X]^+ - C_w W) with W from the FIFO or
+// LIFO issuing equation (Appendix A, reward equation).
 static void build_a_tables(pvi_mdp* p) {
     const int R = p->rad[0], dm = p->dmax[0];
     const auto& P = p->pmf[0];

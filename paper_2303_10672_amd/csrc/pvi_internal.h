@@ -182,7 +182,7 @@ struct B1Dev {
     int32_t* pi;
     double* gap;
     double* partials;     // [nslots][4]
-    int32_t nslots;       // NB * max(ceil(NA / 256), ceil(na1 / kB1Groups))
+    int32_t nslots;       // max(NB ceil(NA / 256), ceil(NA / 64) ceil(NB / 64)): either last grid
     double* w;            // b-side sums over h_b < I_b of V per next A part: general
                           // kernels [Ra][Rb][NB][na1], matrix kernels [NB][na1][nap]
     double* y;            // the b-runs-out term per I_b: general kernels
