@@ -263,7 +263,7 @@ __device__ __forceinline__ void c_merge23_short(unsigned char* smem, const doubl
 // time, so the entries of a lane's vectors sit at constant offsets and only the cap costs
 // address arithmetic.  Cube and slab take
 // 148 KB at RC = 21 in FP64, so one workgroup of up to 14 wavefronts per CU.
-// Measured at R = 21, m = 5 (2.5 GB written): 0.74 ms, 3.4 TB/s; the plain kernel, with one
+// Measured at R = 21, m = 5 (2.5 GB written): 0.68 ms, 3.7 TB/s; the plain kernel, with one
 // LDS read per multiply-add, took 1.41 ms.
 template <typename VT, int RC>
 __global__ __launch_bounds__(1024) void c_merge23_tri_kernel(CDev p, const void* u_, void* out_) {
@@ -375,8 +375,8 @@ __global__ __launch_bounds__(1024) void c_merge23_tri_kernel(CDev p, const void*
 // the order 0, 1, .., a; its lane then updates the state's best (second best, argmax)
 // in LDS, orders ascending.  The slabs T_{m-2}(y_m, z, lo; r') come into LDS straight from
 // memory, the next one while this one is used.
-// Bound by reading T_{m-2} once (2.5 GB in FP64 at R = 21, m = 5): 0.65 ms, 3.9 TB/s; the
-// plain kernel, with one LDS read per multiply-add, took 0.70 ms for the sweeps and the
+// Bound by reading T_{m-2} once (2.5 GB in FP64 at R = 21, m = 5): 0.64 ms, 4.0 TB/s; the
+// plain kernel, with one LDS read per multiply-add, took 0.71 ms for the sweeps and the
 // extraction ran the unfused chain.
 template <typename VT, int RC, bool EXTRACT>
 __global__ __launch_bounds__(64 * kTopWaves) void c_top_kernel(CDev p, const void* in_,
